@@ -512,9 +512,14 @@ struct BwdWs {
   uint64_t rope, dgu, dxn2, dh1, dh1_f32, dctx, delta, dqkv, dxn1, partial, dxn2_send, dxn1_send, dkv, dwpart, total;
 };
 
+// fp32 partials of a GEMM cut into `splits` parts.
+uint64_t partial_bytes(int64_t M, int64_t N, int splits, bool acc_f32) {
+  return splits <= 1 ? 0 : (uint64_t)(acc_f32 ? splits - 1 : splits) * M * N * 4;
+}
+
 uint64_t split_ws_bytes(int64_t M, int64_t N, int64_t K, bool acc_f32 = true) {
-  const int s = gemm_ksplits(M, N, K, acc_f32);
-  return s <= 1 ? 0 : (uint64_t)(acc_f32 ? s - 1 : s) * M * N * 4;
+  const EpiKind kind = acc_f32 ? EpiKind::AccF32 : EpiKind::StoreBF16;
+  return partial_bytes(M, N, gemm_plan(M, N, K, kind, gemm_max_splits(M, N, K, acc_f32)).splits, acc_f32);
 }
 
 FwdWs plan_fwd(const Shard& x, const l4d_peer_outputs* sends) {
@@ -579,15 +584,34 @@ extern "C" int l4d_layer_workspace_bytes(const l4d_model* m, const l4d_parallel*
 }
 
 namespace {
-// A K-contiguous x N-contiguous GEMM whose K is long but not a multiple of 128
-// (the LM head's d_hidden over a vocabulary shard) runs its first K - K % 128 on
-// the BK = 64 kernel and the rest on the ragged-K kernel, summing in fp32.
-bool ragged_k_split(int64_t K) { return K % 128 != 0 && K >= 1024; }
+constexpr uint64_t kScratchBytes = 64ull << 20;   // lm_head_xent_noalloc's static workspace
+
+// Workspace of lm_head_xent.  `least` bytes are always enough: the bf16 logits,
+// plus n x h floats when the vocabulary shard is long and not a multiple of
+// 128.  `full` adds the fp32 partials of d_hidden, whose K range (the vocabulary
+// shard) is cut into `splits` parts where few token rows give few tiles.  The
+// split depends on the sizes alone -- where the logits fit the static workspace,
+// on what is left of it -- so that both entry points sum in the same order.
+struct LmWs {
+  uint64_t logits, least, full;
+  int splits;
+};
+LmWs plan_lm(int64_t n, int64_t h, int64_t v_t) {
+  constexpr uint64_t kMaxSplits = 8;
+  LmWs w;
+  const uint64_t part = std::max<uint64_t>((uint64_t)n * h * 4, 1);
+  w.logits = align_up((uint64_t)n * v_t * 2);
+  w.least = w.logits + (v_t % 128 != 0 && v_t >= 1024 ? align_up((uint64_t)n * h * 4) : 0);
+  const uint64_t cap = w.logits <= kScratchBytes ? std::min(kMaxSplits, (kScratchBytes - w.logits) / part) : kMaxSplits;
+  w.splits = n > 0 ? gemm_plan(n, h, v_t, EpiKind::StoreBF16, (int)std::max<uint64_t>(cap, 1)).splits : 1;
+  w.full = std::max(w.least, align_up(w.logits + partial_bytes(n, h, w.splits, false)));
+  return w;
+}
 }  // namespace
 
 extern "C" int l4d_lm_head_workspace_bytes(int64_t n, int64_t h, int64_t v_t, uint64_t* bytes) {
   if (n < 0 || h <= 0 || v_t <= 0) return fail(L4D_EINVAL, "bad LM-head sizes");
-  if (bytes) *bytes = align_up((uint64_t)n * v_t * 2) + (ragged_k_split(v_t) ? align_up((uint64_t)n * h * 4) : 0);
+  if (bytes) *bytes = plan_lm(n, h, v_t).full;
   return L4D_OK;
 }
 
@@ -635,10 +659,10 @@ inline EpiParams epi_store(void* c, int64_t ldc) {
   return e;
 }
 
-// split_ws: room for the fp32 partials of a split K range (AccF32 only; NULL =
-// never split); split_ws_bytes(M, N, K) bytes are needed.
+// split_ws: room for the fp32 partials of a K range cut into at most max_splits
+// parts (AccF32 and StoreBF16 only; 0 = the layer's rule; NULL = never split).
 int run_gemm(const char* name, hipStream_t s, int64_t M, int64_t N, int64_t K, Operand A, Layout la, Operand B,
-             Layout lb, EpiParams e, float* split_ws = nullptr) {
+             Layout lb, EpiParams e, float* split_ws = nullptr, int max_splits = 0) {
   GemmParams p{};
   p.M = (int32_t)M;
   p.N = (int32_t)N;
@@ -647,10 +671,12 @@ int run_gemm(const char* name, hipStream_t s, int64_t M, int64_t N, int64_t K, O
   p.B = B;
   p.epi = e;
   const bool acc = e.kind == EpiKind::AccF32;
-  if ((acc || e.kind == EpiKind::StoreBF16) && split_ws) {
-    p.k_splits = gemm_ksplits(M, N, K, acc);
-    p.partial = split_ws;
-  }
+  if (!split_ws || !(acc || e.kind == EpiKind::StoreBF16)) max_splits = 1;
+  else if (max_splits == 0) max_splits = gemm_max_splits(M, N, K, acc);
+  const GemmPlan plan = gemm_plan(M, N, K, e.kind, max_splits);
+  p.tile = plan.tile;
+  p.k_splits = plan.splits;
+  p.partial = split_ws;
   int rc = launch(name, s, [&] { return gemm(p, la, lb, s); });
   if (rc || p.k_splits <= 1) return rc;
   return launch("gemm_splitk_reduce", s, [&] {
@@ -988,12 +1014,6 @@ extern "C" int llama_layer_bwd(const l4d_model* m, const l4d_parallel* p, const 
 // ============================================================== LM head
 
 namespace {
-// Bytes of workspace the LM head needs: the bf16 logits, plus an fp32 n x h
-// sum of d_hidden when the vocabulary shard has a ragged tail (ragged_k_split).
-uint64_t lm_xent_ws_bytes(int64_t n, int64_t h, int64_t v_t) {
-  return align_up((uint64_t)n * v_t * 2) + (ragged_k_split(v_t) ? align_up((uint64_t)n * h * 4) : 0);
-}
-
 int lm_xent_check(int64_t n, int64_t h, int64_t v_t, int64_t v0, const void* hidden, const void* w_lm,
                   const int64_t* targets, const float* peer_lse, const float* peer_z, const float* loss,
                   const void* d_hidden, const float* d_w) {
@@ -1007,16 +1027,15 @@ int lm_xent_check(int64_t n, int64_t h, int64_t v_t, int64_t v0, const void* hid
   return L4D_OK;
 }
 
-// The LM-head kernel sequence over lm_xent_ws_bytes(n, h, v_t) bytes of
+// The LM-head kernel sequence over `bytes` >= plan_lm(n, h, v_t).least bytes of
 // device workspace at ws (256-byte aligned; nothing in it needs to start at
 // zero: every byte is written before it is read).
 int lm_xent_run(int64_t n, int64_t h, int64_t v_t, int64_t v0, const void* hidden, const void* w_lm,
                 const int64_t* targets, const float* peer_lse, const float* peer_z, float grad_scale, float* loss,
-                void* d_hidden, float* d_w, uint8_t* ws, hipStream_t s) {
-  const uint64_t logit_bytes = align_up((uint64_t)n * v_t * 2);
-  const bool split_k = ragged_k_split(v_t);
+                void* d_hidden, float* d_w, uint8_t* ws, uint64_t bytes, hipStream_t s) {
+  const LmWs plan = plan_lm(n, h, v_t);
   uint16_t* logits = reinterpret_cast<uint16_t*>(ws);
-  float* dh_f32 = split_k ? reinterpret_cast<float*>(ws + logit_bytes) : nullptr;
+  float* partial = plan.splits > 1 && bytes >= plan.full ? reinterpret_cast<float*>(ws + plan.logits) : nullptr;
   int rc;
   if ((rc = run_gemm("gemm_lm_logits", s, n, v_t, h, op(RowSrc::plain(hidden, h), n), Layout::KC,
                      op(RowSrc::plain(w_lm, h), v_t), Layout::KC, epi_store(logits, v_t))))
@@ -1025,29 +1044,9 @@ int lm_xent_run(int64_t n, int64_t h, int64_t v_t, int64_t v0, const void* hidde
          return xent_rows(logits, n, (int32_t)v_t, v0, targets, peer_lse, peer_z, grad_scale, loss, logits, s);
        })))
     return rc;
-  if (!split_k) {
-    if ((rc = run_gemm("gemm_lm_dx", s, n, h, v_t, op(RowSrc::plain(logits, v_t), n), Layout::KC,
-                       op(RowSrc::plain(w_lm, h), h), Layout::MN, epi_store(d_hidden, h))))
-      return rc;
-  } else {
-    // d_hidden = dlogits[:, :K1] W_lm[:K1] + dlogits[:, K1:] W_lm[K1:] in fp32, then bf16
-    const int64_t k1 = v_t - v_t % 128, k2 = v_t - k1;
-    EpiParams ef{};
-    ef.kind = EpiKind::StoreF32;
-    ef.c = dh_f32;
-    ef.ldc = h;
-    if ((rc = run_gemm("gemm_lm_dx", s, n, h, k1, op(RowSrc::plain(logits, v_t), n), Layout::KC,
-                       op(RowSrc::plain(w_lm, h), h), Layout::MN, ef)))
-      return rc;
-    if ((rc = run_gemm("gemm_lm_dx_tail", s, n, h, k2, op(RowSrc::plain(logits + k1, v_t), n), Layout::KC,
-                       op(RowSrc::plain(static_cast<const uint16_t*>(w_lm) + k1 * h, h), h), Layout::MN,
-                       epi_acc(dh_f32, h))))
-      return rc;
-    if ((rc = launch("gemm_splitk_reduce", s, [&] {
-           return gemm_split_store(static_cast<uint16_t*>(d_hidden), h, dh_f32, n, h, 1, s);
-         })))
-      return rc;
-  }
+  if ((rc = run_gemm("gemm_lm_dx", s, n, h, v_t, op(RowSrc::plain(logits, v_t), n), Layout::KC,
+                     op(RowSrc::plain(w_lm, h), h), Layout::MN, epi_store(d_hidden, h), partial, plan.splits)))
+    return rc;
   return run_gemm("gemm_lm_dw", s, v_t, h, n, op(RowSrc::plain(logits, v_t), v_t), Layout::MN,
                   op(RowSrc::plain(hidden, h), h), Layout::MN, epi_acc(d_w, h));
 }
@@ -1055,7 +1054,6 @@ int lm_xent_run(int64_t n, int64_t h, int64_t v_t, int64_t v0, const void* hidde
 // Workspace of lm_head_xent_noalloc: one array per device, held by the loaded
 // code object until the process ends.  Host code must use the address that
 // hipGetSymbolAddress returns for the current device, never the array's name.
-constexpr uint64_t kScratchBytes = 64ull << 20;
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -1086,10 +1084,15 @@ extern "C" int lm_head_xent(int64_t n, int64_t h, int64_t v_t, int64_t v0, const
   if (rc) return rc;
   if (!A) return fail(L4D_EINVAL, "arena is required");
   if (n == 0) return L4D_OK;
+  // an arena without room for the partials of d_hidden still runs the call, unsplit
+  const LmWs plan = plan_lm(n, h, v_t);
   Workspace ws;
-  if ((rc = take_ws(A, lm_xent_ws_bytes(n, h, v_t), ws))) return rc;
+  ws.A = A;
+  ws.size = plan.full;
+  ws.held = arena_alloc(A, ws.size, &ws.off);
+  if (!ws.held && (rc = take_ws(A, plan.least, ws))) return rc;
   return lm_xent_run(n, h, v_t, v0, hidden, w_lm, targets, peer_lse, peer_z, grad_scale, loss, d_hidden, d_w,
-                     reinterpret_cast<uint8_t*>(A->base + ws.off), static_cast<hipStream_t>(stream_ptr));
+                     reinterpret_cast<uint8_t*>(A->base + ws.off), ws.size, static_cast<hipStream_t>(stream_ptr));
 }
 
 extern "C" int lm_head_xent_noalloc(int64_t n, int64_t h, int64_t v_t, int64_t v0, const void* hidden,
@@ -1098,7 +1101,7 @@ extern "C" int lm_head_xent_noalloc(int64_t n, int64_t h, int64_t v_t, int64_t v
                                     void* stream_ptr) {
   int rc = lm_xent_check(n, h, v_t, v0, hidden, w_lm, targets, peer_lse, peer_z, loss, d_hidden, d_w);
   if (rc) return rc;
-  const uint64_t need = lm_xent_ws_bytes(n, h, v_t);
+  const uint64_t need = plan_lm(n, h, v_t).least;
   if (need > kScratchBytes)
     return fail(L4D_EINVAL, "LM head needs %llu bytes of workspace; the static scratch holds %llu",
                 (unsigned long long)need, (unsigned long long)kScratchBytes);
@@ -1106,7 +1109,7 @@ extern "C" int lm_head_xent_noalloc(int64_t n, int64_t h, int64_t v_t, int64_t v
   uint8_t* ws = nullptr;
   if ((rc = scratch_on_current_device(&ws))) return rc;
   return lm_xent_run(n, h, v_t, v0, hidden, w_lm, targets, peer_lse, peer_z, grad_scale, loss, d_hidden, d_w, ws,
-                     static_cast<hipStream_t>(stream_ptr));
+                     kScratchBytes, static_cast<hipStream_t>(stream_ptr));
 }
 
 // ============================================================== the ends of the model
@@ -1250,8 +1253,6 @@ extern "C" int lm_head_bwd(const l4d_model* m, const l4d_parallel* p, const void
   const uint64_t o_dl = cv.take((uint64_t)tok * v_t * 2), o_dxn = cv.take((uint64_t)rows_sp * x.h * 2);
   const uint64_t o_part = cv.take((uint64_t)npart * x.h * 4);
   const uint64_t o_send = (x.t > 1 && !dxn_send) ? cv.take((uint64_t)x.b * (x.t - 1) * x.s_sp * x.h * 2) : 0;
-  const bool split_k = ragged_k_split(v_t);
-  const uint64_t o_sum = split_k ? cv.take((uint64_t)tok * x.h * 4) : 0;
   Workspace ws;
   if ((rc = take_ws(A, cv.used, ws))) return rc;
   uint8_t* wsb = reinterpret_cast<uint8_t*>(A->base + ws.off);
@@ -1264,30 +1265,9 @@ extern "C" int lm_head_bwd(const l4d_model* m, const l4d_parallel* p, const void
        })))
     return rc;
   // d(xn) over the gathered rows: own rows + the peers' partials, the peers' rows sent
-  if (!split_k) {
-    if ((rc = run_gemm("gemm_head_dx", s, tok, x.h, v_t, op(RowSrc::plain(dl, v_t), tok), Layout::KC,
-                       op(RowSrc::plain(w_lm, x.h), x.h), Layout::MN, epi_residual(x, dxn, nullptr, peer_dxn, send))))
-      return rc;
-  } else {   // as in lm_head_xent: the bulk of K on the BK = 64 kernel, the tail on the ragged one, in fp32
-    float* sum = reinterpret_cast<float*>(wsb + o_sum);
-    const int64_t k1 = v_t - v_t % 128, k2 = v_t - k1;
-    EpiParams ef{};
-    ef.kind = EpiKind::StoreF32;
-    ef.c = sum;
-    ef.ldc = x.h;
-    if ((rc = run_gemm("gemm_head_dx", s, tok, x.h, k1, op(RowSrc::plain(dl, v_t), tok), Layout::KC,
-                       op(RowSrc::plain(w_lm, x.h), x.h), Layout::MN, ef)))
-      return rc;
-    if ((rc = run_gemm("gemm_head_dx_tail", s, tok, x.h, k2, op(RowSrc::plain(dl + k1, v_t), tok), Layout::KC,
-                       op(RowSrc::plain(static_cast<const uint16_t*>(w_lm) + k1 * x.h, x.h), x.h), Layout::MN,
-                       epi_acc(sum, x.h))))
-      return rc;
-    if ((rc = launch("sp_finish", s, [&] {
-           return sp_finish(sum, (int32_t)x.h, tok, (int32_t)x.s_c, (int32_t)x.s_sp, (int32_t)x.tr, (int32_t)x.t,
-                            static_cast<const uint16_t*>(peer_dxn), dxn, static_cast<uint16_t*>(send), s);
-         })))
-      return rc;
-  }
+  if ((rc = run_gemm("gemm_head_dx", s, tok, x.h, v_t, op(RowSrc::plain(dl, v_t), tok), Layout::KC,
+                     op(RowSrc::plain(w_lm, x.h), x.h), Layout::MN, epi_residual(x, dxn, nullptr, peer_dxn, send))))
+    return rc;
   if ((rc = launch("rmsnorm_bwd", s, [&] {
          const NormBwdIo io{dxn, nullptr, nullptr, nullptr, static_cast<uint16_t*>(dx), nullptr};
          return rmsnorm_bwd(sptr(st, L4D_HEAD_X), static_cast<const uint16_t*>(w_norm), io, partial, npart,

@@ -1,31 +1,28 @@
 // bf16 GEMM on the gfx950 matrix cores: C[m][n] = sum_k A(m,k) B(n,k), fp32
 // accumulation, with the layer's fused epilogues.
 //
-// A workgroup owns a 256x256 tile of C; each wave accumulates a 128 x (NS*32)
-// block as tiles of v_mfma_f32_32x32x16_bf16.  Operand tiles move global ->
-// LDS by global_load_lds_dwordx4 (direct-to-LDS DMA, one contiguous KB per
-// wave instruction, no staging registers).  Every stage buffer is its own LDS
-// object, so the compiler knows a read of one stage cannot depend on the
-// copies still landing in the others.  Two kernels:
+// Operand tiles move global -> LDS by global_load_lds_dwordx4 (direct-to-LDS
+// DMA, one contiguous KB per wave instruction, no staging registers), in stages
+// of 64 k.  Where K ends inside a stage the copies take zeros instead, so any K
+// runs on the same kernels.  Two kernels:
 //
-//  * gemm_bk64 (K a multiple of 128): two stages of 64 k.  A K-contiguous copy
-//    moves 8 whole 128-byte rows per instruction (one cache line each); the
-//    fragments of the next 16-k sub-step are read from LDS under the MFMAs of
-//    the current one, and the barrier that publishes stage kt+1 sits before
-//    the last sub-step of stage kt, right after which the freed buffers take
-//    stage kt+2 (the A half there, the B half one sub-step later, so the
-//    copies do not all reach the texture path at once).  8 waves (two per
-//    SIMD, 128x64 each) or 4 (128x128 each).
-//  * gemm_bk32 (any K that is a multiple of 8): 8 waves, four stages of 32 k,
-//    16 rows x 64 bytes per copy instruction, the stage past K zeroed in
-//    registers.
+//  * gemm_bk64: a workgroup of 8 waves (two per SIMD) owns a 256x256 tile of C,
+//    each wave a 128x64 block of v_mfma_f32_32x32x16_bf16 tiles; two stages.  A
+//    K-contiguous copy moves 8 whole 128-byte rows per instruction (one cache
+//    line each); the fragments of the next 16-k sub-step are read from LDS under
+//    the MFMAs of the current one, and the barrier that publishes stage kt+1
+//    sits before the last sub-step of stage kt, right after which the freed
+//    buffers take stage kt+2 (the A half there, the B half one sub-step later,
+//    so the copies do not all reach the texture path at once).
+//  * gemm_tile: 128- or 64-row tiles with a deep ring of stages, for the grids
+//    that 256-row tiles would leave mostly empty (gemm_plan picks).
 //
 // Operand layouts: "KC" (reduction index contiguous: activations in the
 // forward, the output gradient in dX) is stored row by row, the 16-byte chunks
 // of a row permuted by an XOR with row bits so that the 16 rows a 16-lane
 // group of a fragment read touches cover all 64 banks (256 bytes) once.  "MN" (reduction
 // index strided: the weight in dX, both operands of dW) is stored as k-rows
-// of 256 columns with the 16-byte chunks XOR-swizzled by row, and read with
+// of the tile's columns with the 16-byte chunks XOR-swizzled by row, and read with
 // two ds_read_b64_tr_b16 that hand each lane 4 consecutive k of one column --
 // the transpose happens in the LDS read, not in registers.
 //
@@ -33,9 +30,8 @@
 // n and n + PAIR land in the same lane and register: a RoPE pair (i, i + d_h/2)
 // or a gate/up pair of the fused FFN weight.  The epilogue stages rows through
 // LDS and hands 8-column vectors to the fused operation, with that operation's
-// global inputs loaded for a whole pass first.  The fp32 accumulate (dW) needs
-// no staging: the C tile meets the accumulators in registers (added at the end
-// in the BK = 64 kernel, loaded before the first product in the BK = 32 one).
+// global inputs loaded for a whole pass first.  The fp32 accumulate (dW) of the
+// 256-row kernel needs no staging: the C tile meets the accumulators in registers.
 #include "kernels.h"
 
 namespace l4d {
@@ -46,14 +42,15 @@ typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // the caller's fp32 arrays: float-aligned
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 #define GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define LPTR(p) ((__attribute__((address_space(3))) void*)(p))
 
-constexpr int BM = 256, BN = 256, BK = 32;
-constexpr int TILE_BYTES = 256 * BK * 2;     // 16 KB per operand per stage
+constexpr int BM = 256, BN = 256;
 constexpr int GROUP_M = 4;
 
 __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
@@ -67,12 +64,18 @@ __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(ui
 // a stage, and before the stages are reused as epilogue staging space.
 // TAG only changes the asm text (a comment), to keep copies in the two arms of
 // a branch from being merged.
+__device__ __forceinline__ uint32_t lds_addr(const uint8_t* lds) {
+  return __builtin_amdgcn_readfirstlane(   // uniform by construction; stated for the compiler
+      static_cast<uint32_t>(reinterpret_cast<uintptr_t>(LPTR(const_cast<uint8_t*>(lds)))));
+}
+template <int TAG = 0>
+__device__ __forceinline__ void dma16(const uint16_t* g, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off ; copy form %2" ::"v"(g), "s"(lds), "n"(TAG)
+               : "memory", "m0");
+}
 template <int TAG = 0>
 __device__ __forceinline__ void dma16(const uint16_t* g, const uint8_t* lds) {
-  const uint32_t l = __builtin_amdgcn_readfirstlane(   // uniform by construction; stated for the compiler
-      static_cast<uint32_t>(reinterpret_cast<uintptr_t>(LPTR(const_cast<uint8_t*>(lds)))));
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off ; copy form %2" ::"v"(g), "s"(l), "n"(TAG)
-               : "memory", "m0");
+  dma16<TAG>(g, lds_addr(lds));
 }
 
 __device__ __forceinline__ u32x4 pack8(const float* v) {
@@ -96,92 +99,44 @@ __device__ __forceinline__ int xcd_remap(int bid, int nwg) {
   return xcd < rem ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
 }
 
+// Sixteen zero bytes: the source of a copy whose k lies past the end of K, so
+// that a ragged K ends in zeros in LDS and the products need no mask (both
+// operands are zero there, so an infinity or NaN elsewhere stays where it is).
+__device__ __align__(16) const uint32_t kZeros[4] = {0u, 0u, 0u, 0u};
+__device__ __forceinline__ const uint16_t* zeros() { return reinterpret_cast<const uint16_t*>(kZeros); }
+
 // ------------------------------------------------------------------ LDS layouts
-// KC tile: row r (0..255) holds its 32 k (64 bytes) at r*64, the four 16-byte
-// chunks permuted by c ^ ((r >> 2) & 3).  Four rows share a 256-byte bank line
-// (r % 4 picks the quarter), so the 16 rows one 16-lane group of a fragment
-// read touches cover all 64 banks once.
-__device__ __forceinline__ int kc_off(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
-// MN tile: k-row r (0..31), 16-byte chunk c (0..31) of its 256 columns,
-// stored at chunk c ^ 4 (r % 4).  A transposing read (32 lanes: 4 k-rows x an
-// aligned group of 4 chunks) then touches 4 different chunk groups, all 64
-// banks once; k-rows r and r + 4 share the pattern.
-__device__ __forceinline__ int mn_swz(int row) { return (row & 3) << 2; }
-__device__ __forceinline__ int mn_off(int row, int chunk) { return row * 512 + ((chunk ^ mn_swz(row)) << 4); }
+// A stage holds 64 k of an operand tile of T rows (T = 256, 128 or 64).
+// KC tile: row r holds its 64 k (128 bytes) at r * 128, chunk c of 16 bytes at
+// slot c ^ ((r >> 1) & 7).  Two rows share a 256-byte bank line (r % 2 picks
+// the half), so the 16 rows one 16-lane group of a fragment read touches cover
+// all 64 banks once.
+constexpr int BK2 = 64;
+constexpr int TILE2 = 256 * BK2 * 2;     // 32 KB per operand per stage of a 256-row tile
 
-// Each stage holds 16 KB per operand; wave w copies LDS KB numbers
-// kb = w + WAVES * q.  KC: KB kb holds tile rows 16 kb + lane/4, 64 contiguous
-// bytes of each row per instruction (4 lanes), lane l fetching the chunk
-// that belongs at its LDS slot l % 4: chunk (l & 3) ^ ((l >> 4) & 3), the
-// same for every q.  A lane's source rows are fixed over K and kept as
-// pointers.  MN: KB kb holds k-rows 2 kb + lane/32.
-template <int WAVES>
-struct KcRows {
-  const uint16_t* row[16 / WAVES];   // source row of copy q (chunk not included)
-  int c8;                            // element offset of the lane's chunk
-};
-
-template <int WAVES>
-__device__ __forceinline__ KcRows<WAVES> kc_rows(const Operand& op, int x0, int tile_idx, int wave, int lane) {
-  KcRows<WAVES> r;
-  r.c8 = 8 * ((lane & 3) ^ ((lane >> 4) & 3));
-#pragma unroll
-  for (int q = 0; q < 16 / WAVES; ++q) {
-    const int xr = 16 * (wave + WAVES * q) + (lane >> 2);
-    int64_t gx;
-    if (op.split_rows) {
-      int i = tile_idx * 128 + (xr & 127);
-      if (i >= op.split_rows) i = op.split_rows - 1;
-      gx = (xr >= 128 ? op.split_off : 0) + i;
-    } else {
-      gx = x0 + xr;
-      if (gx >= op.rows) gx = op.rows - 1;
-    }
-    r.row[q] = op.src.row(gx);
-  }
-  return r;
-}
-
-// RAGGED: K may end inside the stage; the chunks past K copy the last whole
-// chunk instead (those fragments are zeroed before use).
-template <int WAVES, bool RAGGED>
-__device__ __forceinline__ void copy_kc(uint8_t* lds, const KcRows<WAVES>& rows, int k0, int K, int wave) {
-  int k = k0 + rows.c8;
-  if constexpr (RAGGED) k = min(k, K - 8);
-#pragma unroll
-  for (int q = 0; q < 16 / WAVES; ++q)
-    dma16(rows.row[q] + k, lds + (wave + WAVES * q) * 1024);
-}
-
-template <int WAVES>
-__device__ __forceinline__ void copy_mn(uint8_t* lds, const Operand& op, int x0, int k0, int K, int wave,
-                                        int lane) {
-#pragma unroll
-  for (int q = 0; q < 16 / WAVES; ++q) {
-    const int kb = wave + WAVES * q;
-    const int kr = 2 * kb + (lane >> 5);
-    const int lc = (lane & 31) ^ mn_swz(kr);
-    int k = k0 + kr;
-    if (k >= K) k = K - 1;
-    int x = x0 + lc * 8;
-    if (x >= op.rows) x = op.rows - 8;
-    const uint32_t o = op.src.row_index(k);
-    const uint16_t* base = (o & 0x80000000u) ? op.src.peer : op.src.own;
-    dma16(base + static_cast<int64_t>(o & 0x7fffffffu) * op.src.ld + x, lds + kb * 1024);
-  }
-}
+__device__ __forceinline__ int kc2_off(int row, int chunk) { return row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4); }
+// MN tile: k-row r (0..63) of T columns, 16-byte chunk c stored at chunk
+// c ^ mn_swz(r).  A transposing read (32 lanes: 4 k-rows x an aligned group of
+// 4 chunks) then touches all 64 banks once: with T >= 128 a row spans whole
+// bank lines and the 4 rows take 4 different chunk groups; with T = 64 a row is
+// half a line, r % 2 picks the half and the swizzle separates rows r and r + 2.
+// k-rows r and r + 4 share the pattern.
+template <int T>
+__device__ __forceinline__ int mn_swz(int row) { return T >= 128 ? (row & 3) << 2 : (row & 2) << 1; }
+template <int T>
+__device__ __forceinline__ int mn_off(int row, int chunk) { return row * (2 * T) + ((chunk ^ mn_swz<T>(row)) << 4); }
 
 // MFMA operand for rows x0 + lane%32 (x0 a multiple of 32), k = 16 kk + 8 (lane/32) + 0..7.
-template <Layout L>
+template <Layout L, int T>
 __device__ __forceinline__ bf16x8 frag(const uint8_t* lds, int x0, int kk, int lane) {
   if constexpr (L == Layout::KC) {
-    return *reinterpret_cast<const bf16x8*>(lds + kc_off(x0 + (lane & 31), 2 * kk + (lane >> 5)));
+    return *reinterpret_cast<const bf16x8*>(lds + kc2_off(x0 + (lane & 31), 2 * kk + (lane >> 5)));
   } else {
     const int li = lane & 15;
     const int row = 16 * kk + 8 * (lane >> 5) + (li >> 2);
     const int x = x0 + 16 * ((lane >> 4) & 1) + 4 * (li & 3);
-    const int off = mn_off(row, x >> 3) + ((x & 7) << 1);
-    const int off4 = mn_off(row + 4, x >> 3) + ((x & 7) << 1);
+    const int off = mn_off<T>(row, x >> 3) + ((x & 7) << 1);
+    const int off4 = mn_off<T>(row + 4, x >> 3) + ((x & 7) << 1);
     const i16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
         reinterpret_cast<__attribute__((address_space(3))) i16x4*>(LPTR(const_cast<uint8_t*>(lds) + off)));
     const i16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
@@ -214,6 +169,10 @@ template <>
 struct EpiIn<EpiKind::QkvRope> {
   float4 cs[4];           // (cos, sin) of the 8 columns
 };
+template <>
+struct EpiIn<EpiKind::AccF32> {
+  f32x4 c[4];             // the accumulator: low and high half
+};
 
 // Output row of logical row m for ResidualSP: own rows map into own_out,
 // the others into the send buffer.
@@ -227,18 +186,18 @@ __device__ __forceinline__ int64_t resid_row(const EpiParams& e, int64_t m, bool
   return own ? bi * e.s_sp + (i - lo_row) : bi * static_cast<int64_t>(e.t - 1) * e.s_sp + (i < lo_row ? i : i - e.s_sp);
 }
 
-template <EpiKind KIND, int PAIR>
-__device__ __forceinline__ void epi_load(const GemmParams& p, int64_t m, int tn, int col, EpiIn<KIND>& in) {
+// The two halves start at columns n_lo and n_lo + pair.
+template <EpiKind KIND>
+__device__ __forceinline__ void epi_load(const GemmParams& p, int64_t m, int n_lo, int pair, EpiIn<KIND>& in) {
   const EpiParams& e = p.epi;
   if (m >= p.M) return;
-  const int n_lo = tn * BN + col;
   if constexpr (KIND == EpiKind::ResidualSP) {
     bool own;
     const int64_t orow = resid_row(e, m, own);
     if (!own) return;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int n = n_lo + h * PAIR;
+      const int n = n_lo + h * pair;
       if (n >= p.N) continue;
       const int64_t off = orow * e.ldc + n;
       if (e.resid) in.r[h] = *reinterpret_cast<const u32x4*>(e.resid + off);
@@ -247,12 +206,21 @@ __device__ __forceinline__ void epi_load(const GemmParams& p, int64_t m, int tn,
   } else if constexpr (KIND == EpiKind::SwiGLUBwd) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int n = n_lo + h * PAIR;
+      const int n = n_lo + h * pair;
       if (n >= p.N) continue;
       const int64_t off = m * e.f + n;
       in.g[h] = *reinterpret_cast<const u32x4*>(e.g_in + off);
       in.u[h] = *reinterpret_cast<const u32x4*>(e.u_in + off);
       in.a[h] = *reinterpret_cast<const u32x4*>(e.act_in + off);
+    }
+  } else if constexpr (KIND == EpiKind::AccF32) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int n = n_lo + h * pair;
+      if (n >= p.N) continue;
+      const f32x4_a4* c = reinterpret_cast<const f32x4_a4*>(static_cast<const float*>(e.c) + m * e.ldc + n);
+      in.c[2 * h] = c[0];
+      in.c[2 * h + 1] = c[1];
     }
   } else if constexpr (KIND == EpiKind::QkvRope) {
     if (n_lo >= p.N || n_lo >= e.nq + e.nk) return;     // V columns are not rotated
@@ -264,18 +232,17 @@ __device__ __forceinline__ void epi_load(const GemmParams& p, int64_t m, int tn,
   }
 }
 
-// lo: 8 columns starting at tile column `col`; hi: the 8 columns PAIR further.
-template <EpiKind KIND, int PAIR>
-__device__ __forceinline__ void epilogue(const GemmParams& p, int64_t m, int tn, int col, float* lo, float* hi,
+// lo: 8 columns starting at column n_lo; hi: the 8 columns `pair` further.
+template <EpiKind KIND>
+__device__ __forceinline__ void epilogue(const GemmParams& p, int64_t m, int n_lo, int pair, float* lo, float* hi,
                                          const EpiIn<KIND>& in) {
   const EpiParams& e = p.epi;
   if (m >= p.M) return;
-  const int n_lo = tn * BN + col;
   switch (KIND) {
     case EpiKind::StoreBF16: {
       uint16_t* c = static_cast<uint16_t*>(e.c) + m * e.ldc;
       if (n_lo < p.N) *reinterpret_cast<u32x4*>(c + n_lo) = pack8(lo);
-      if (n_lo + PAIR < p.N) *reinterpret_cast<u32x4*>(c + n_lo + PAIR) = pack8(hi);
+      if (n_lo + pair < p.N) *reinterpret_cast<u32x4*>(c + n_lo + pair) = pack8(hi);
       break;
     }
     case EpiKind::StoreF32: {
@@ -284,17 +251,30 @@ __device__ __forceinline__ void epilogue(const GemmParams& p, int64_t m, int tn,
         *reinterpret_cast<float4*>(c + n_lo) = make_float4(lo[0], lo[1], lo[2], lo[3]);
         *reinterpret_cast<float4*>(c + n_lo + 4) = make_float4(lo[4], lo[5], lo[6], lo[7]);
       }
-      if (n_lo + PAIR < p.N) {
-        *reinterpret_cast<float4*>(c + n_lo + PAIR) = make_float4(hi[0], hi[1], hi[2], hi[3]);
-        *reinterpret_cast<float4*>(c + n_lo + PAIR + 4) = make_float4(hi[4], hi[5], hi[6], hi[7]);
+      if (n_lo + pair < p.N) {
+        *reinterpret_cast<float4*>(c + n_lo + pair) = make_float4(hi[0], hi[1], hi[2], hi[3]);
+        *reinterpret_cast<float4*>(c + n_lo + pair + 4) = make_float4(hi[4], hi[5], hi[6], hi[7]);
       }
       break;
     }
-    case EpiKind::AccF32:     // handled in registers (acc_load_f32 / acc_store_f32)
+    case EpiKind::AccF32: {   // the 256-row kernel adds in registers instead (acc_add_store_f32)
+      if constexpr (KIND == EpiKind::AccF32) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int n = n_lo + h * pair;
+          if (n >= p.N) continue;
+          const float* src = h ? hi : lo;
+          float* c = static_cast<float*>(e.c) + m * e.ldc + n;
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+            *reinterpret_cast<f32x4_a4*>(c + 4 * q) = in.c[2 * h + q] + f32x4{src[4 * q], src[4 * q + 1], src[4 * q + 2], src[4 * q + 3]};
+        }
+      }
       break;
+    }
     case EpiKind::QkvRope: {
       if constexpr (KIND == EpiKind::QkvRope) {
-        // n_lo lies in the first half of a head, n_lo + PAIR (PAIR = d_h/2) in the second.
+        // n_lo lies in the first half of a head, n_lo + pair (pair = d_h/2) in the second.
         if (n_lo >= p.N) break;
         uint16_t* dst;
         int64_t ld;
@@ -313,10 +293,10 @@ __device__ __forceinline__ void epilogue(const GemmParams& p, int64_t m, int tn,
             b[j] = hi[j] * c + lo[j] * sn;
           }
           *reinterpret_cast<u32x4*>(dst + m * ld + n) = pack8(a);
-          *reinterpret_cast<u32x4*>(dst + m * ld + n + PAIR) = pack8(b);
+          *reinterpret_cast<u32x4*>(dst + m * ld + n + pair) = pack8(b);
         } else {
           *reinterpret_cast<u32x4*>(dst + m * ld + n) = pack8(lo);
-          *reinterpret_cast<u32x4*>(dst + m * ld + n + PAIR) = pack8(hi);
+          *reinterpret_cast<u32x4*>(dst + m * ld + n + pair) = pack8(hi);
         }
       }
       break;
@@ -327,7 +307,7 @@ __device__ __forceinline__ void epilogue(const GemmParams& p, int64_t m, int tn,
         const int64_t orow = resid_row(e, m, own);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const int n = n_lo + h * PAIR;
+          const int n = n_lo + h * pair;
           if (n >= p.N) continue;
           float* src = h ? hi : lo;
           const int64_t off = orow * e.ldc + n;
@@ -358,7 +338,7 @@ __device__ __forceinline__ void epilogue(const GemmParams& p, int64_t m, int tn,
       break;
     }
     case EpiKind::SwiGLUFwd: {
-      const int j = tn * 128 + col;       // FFN column of this gate/up pair
+      const int j = n_lo;                 // FFN column of this gate/up pair
       if (j >= e.f) break;
       const int64_t off = m * e.f + j;
       float g[8], u[8], a[8], pr[8];
@@ -379,7 +359,7 @@ __device__ __forceinline__ void epilogue(const GemmParams& p, int64_t m, int tn,
       if constexpr (KIND == EpiKind::SwiGLUBwd) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const int n = n_lo + h * PAIR;
+          const int n = n_lo + h * pair;
           if (n >= p.N) continue;
           const float* dp = h ? hi : lo;
           const int64_t off = m * e.f + n;
@@ -438,6 +418,10 @@ __device__ __forceinline__ void wait_vm() {
   else asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
 }
 
+// First column of tile tn: a gate/up tile holds 128 FFN columns of each half.
+template <EpiKind KIND>
+__device__ __forceinline__ int n_first(int tn) { return KIND == EpiKind::SwiGLUFwd ? tn * 128 : tn * BN; }
+
 // Epilogue: each wave stages R rows x (NS*32) columns of fp32 at a time in its
 // own 16 KB of LDS (column halves swapped on rows with bit 2 set, so the two
 // half-waves write different banks) and hands out 8-column vectors of its low
@@ -457,7 +441,7 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, f32x16 (&acc)[4]
     for (int it = 0; it < ITERS; ++it) {
       const int idx = it * 64 + lane;
       const int rr = idx / ((NS / 2) * 4), v = idx % ((NS / 2) * 4);
-      epi_load<KIND, PAIR>(p, row0 + pass * R + rr, tn, ncol[v >> 2] + (v & 3) * 8, in[it]);
+      epi_load<KIND>(p, row0 + pass * R + rr, n_first<KIND>(tn) + ncol[v >> 2] + (v & 3) * 8, PAIR, in[it]);
     }
 #pragma unroll
     for (int mm = 0; mm < MS_PER; ++mm)
@@ -481,55 +465,19 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, f32x16 (&acc)[4]
       const float4 l0 = lo4[0], l1 = lo4[1], h0 = hi4[0], h1 = hi4[1];
       float lo[8] = {l0.x, l0.y, l0.z, l0.w, l1.x, l1.y, l1.z, l1.w};
       float hi[8] = {h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w};
-      epilogue<KIND, PAIR>(p, row0 + pass * R + rr, tn, ncol[j] + c8, lo, hi, in[it]);
+      epilogue<KIND>(p, row0 + pass * R + rr, n_first<KIND>(tn) + ncol[j] + c8, PAIR, lo, hi, in[it]);
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);
   }
 }
 
-// AccF32 (C += A B^T in fp32) works on the accumulators directly.  In the BK =
-// 32 kernel the tile of C is loaded into them before the first product (its
-// latency overlaps the first stage's copies) and stored from them at the end;
-// the BK = 64 kernel adds it at the end (acc_add_store_f32).  In the accumulator layout
-// the 32 lanes of a half-wave cover 32 consecutive columns (128 bytes) of one
-// row, so both are whole-line accesses without staging.  Whole tiles load and
-// store non-temporally: each C element is touched once per launch, and
-// streaming it leaves L2 to the operand tiles the neighbouring workgroups share
-// (4-5% off the largest weight-gradient GEMM of the Llama-2-7B layer).
-template <int NS>
-__device__ __forceinline__ void acc_load_f32(f32x16 (&acc)[4][NS], const GemmParams& p, const float* cbase,
-                                             int64_t ldc, int64_t row0, int tn, const int* ncol, int lane) {
-  const int rl = 4 * (lane >> 5);
-  int32_t off[NS];            // lane's element offset from its row block's first row
-#pragma unroll
-  for (int ns = 0; ns < NS; ++ns) off[ns] = static_cast<int32_t>(rl * ldc) + tn * BN + ncol[ns] + (lane & 31);
-  const bool full = row0 + 128 <= p.M && (tn + 1) * BN <= p.N;   // uniform
-  if (full) {
-#pragma unroll
-    for (int ms = 0; ms < 4; ++ms)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int r = ms * 32 + 8 * (i >> 2) + (i & 3);
-        const float* row = cbase + (row0 + r) * ldc;   // uniform
-#pragma unroll
-        for (int ns = 0; ns < NS; ++ns) acc[ms][ns][i] = __builtin_nontemporal_load(&row[off[ns]]);
-      }
-  } else {
-#pragma unroll
-    for (int ms = 0; ms < 4; ++ms)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int r = ms * 32 + 8 * (i >> 2) + (i & 3);
-        const float* row = cbase + (row0 + r) * ldc;   // uniform
-#pragma unroll
-        for (int ns = 0; ns < NS; ++ns) {
-          const int n = tn * BN + ncol[ns] + (lane & 31);
-          acc[ms][ns][i] = (row0 + r + rl < p.M && n < p.N) ? row[off[ns]] : 0.0f;
-        }
-      }
-  }
-}
-
+// AccF32 (C += A B^T in fp32) of the 256-row kernel works on the accumulators
+// directly: in the accumulator layout the 32 lanes of a half-wave cover 32
+// consecutive columns (128 bytes) of one row, so loads and stores are
+// whole-line accesses without staging.  Whole tiles load and store
+// non-temporally: each C element is touched once per launch, and streaming it
+// leaves L2 to the operand tiles the neighbouring workgroups share (4-5% off
+// the largest weight-gradient GEMM of the Llama-2-7B layer).
 template <int NS>
 __device__ __forceinline__ void acc_store_f32(const f32x16 (&acc)[4][NS], const GemmParams& p, float* cbase,
                                               int64_t ldc, int64_t row0, int tn, const int* ncol, int lane) {
@@ -611,18 +559,6 @@ __device__ __forceinline__ void acc_add_store_f32(const f32x16 (&acc)[4][NS], co
     }
 }
 
-// Ends the accumulators' pending loads here: an asm that reads and redefines
-// them makes the compiler wait for the loads before it, once, instead of at
-// their first use inside the main loop on every iteration (where the counter
-// also holds the copies of the next stages).
-template <int NS>
-__device__ __forceinline__ void settle_acc(f32x16 (&acc)[4][NS]) {
-#pragma unroll
-  for (int ms = 0; ms < 4; ++ms)
-#pragma unroll
-    for (int ns = 0; ns < NS; ++ns) asm volatile("" : "+v"(acc[ms][ns]));
-}
-
 struct TileCoord {
   int tm, tn;
 };
@@ -639,124 +575,7 @@ __device__ __forceinline__ TileCoord tile_of(const GemmParams& p) {
   return tile_coord(p, xcd_remap(blockIdx.x, gridDim.x));
 }
 
-// 8 waves (two per SIMD), each 128 x 64.
-template <Layout LA, Layout LB, EpiKind KIND, int PAIR>
-__global__ void __launch_bounds__(512, 1) gemm_bk32(GemmParams p) {
-  constexpr int WAVES = 8, NS = 2, PER = 2;
-  constexpr bool RAGGED = true;
-  __shared__ __attribute__((aligned(16))) uint8_t a0[TILE_BYTES], b0[TILE_BYTES], a1[TILE_BYTES], b1[TILE_BYTES];
-  __shared__ __attribute__((aligned(16))) uint8_t a2[TILE_BYTES], b2[TILE_BYTES], a3[TILE_BYTES], b3[TILE_BYTES];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform per wave: scalar code for wave-level decisions
-  const TileCoord tc = tile_of(p);
-  const int tm = tc.tm, tn = tc.tn, m0 = tm * BM, n0 = tn * BN;
-  const int wm = wave >> 2, wn = wave & 3;
-  int ncol[NS];
-  ncol[0] = lo_col<WAVES, PAIR>(wn, 0);
-  ncol[1] = ncol[0] + PAIR;
-
-  f32x16 acc[4][NS];
-  if constexpr (KIND == EpiKind::AccF32) {
-    acc_load_f32<NS>(acc, p, static_cast<float*>(p.epi.c), p.epi.ldc, static_cast<int64_t>(m0) + wm * 128, tn,
-                     ncol, lane);
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < NS; ++j) acc[i][j] = f32x16{};
-  }
-
-  KcRows<WAVES> ra{}, rb{};
-  if constexpr (LA == Layout::KC) ra = kc_rows<WAVES>(p.A, m0, tm, wave, lane);
-  if constexpr (LB == Layout::KC) rb = kc_rows<WAVES>(p.B, n0, tn, wave, lane);
-
-  auto issue = [&](int k0, uint8_t* la, uint8_t* lb) {
-    if constexpr (LA == Layout::KC) copy_kc<WAVES, RAGGED>(la, ra, k0, p.K, wave);
-    else copy_mn<WAVES>(la, p.A, m0, k0, p.K, wave, lane);
-    if constexpr (LB == Layout::KC) copy_kc<WAVES, RAGGED>(lb, rb, k0, p.K, wave);
-    else copy_mn<WAVES>(lb, p.B, n0, k0, p.K, wave, lane);
-  };
-  auto compute = [&](int k0, const uint8_t* la, const uint8_t* lb) {
-    const bool tail = k0 + BK > p.K;     // uniform: only the last step of a ragged K
-#pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      bf16x8 af[4], bf[NS];
-#pragma unroll
-      for (int ms = 0; ms < 4; ++ms) af[ms] = frag<LA>(la, wm * 128 + ms * 32, kk, lane);
-#pragma unroll
-      for (int ns = 0; ns < NS; ++ns) bf[ns] = frag<LB>(lb, ncol[ns], kk, lane);
-      if (tail) {
-        const bool z = k0 + 16 * kk + 8 * (lane >> 5) >= p.K;
-#pragma unroll
-        for (int ms = 0; ms < 4; ++ms) af[ms] = z ? bf16x8{} : af[ms];
-#pragma unroll
-        for (int ns = 0; ns < NS; ++ns) bf[ns] = z ? bf16x8{} : bf[ns];
-      }
-#pragma unroll
-      for (int ms = 0; ms < 4; ++ms)
-#pragma unroll
-        for (int ns = 0; ns < NS; ++ns)
-          acc[ms][ns] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ms], bf[ns], acc[ms][ns], 0, 0, 0);
-    }
-  };
-
-  // Step kt reads stage kt % 4.  On entry to a step the copies of the next two
-  // steps may still be in flight (2 * PER instructions per operand each):
-  // wait until only those remain, then a barrier makes every wave's copy of
-  // this step visible and frees the stage of step kt - 1 for step kt + 3.
-  const int nk = (p.K + BK - 1) / BK;
-  auto step = [&](int kt, const uint8_t* la, const uint8_t* lb, uint8_t* na, uint8_t* nb) {
-    const int after = nk - 1 - kt;
-    if (after >= 2) wait_vm<4 * PER>();
-    else if (after == 1) wait_vm<2 * PER>();
-    else wait_vm<0>();
-    stage_barrier();
-    if (kt + 3 < nk) issue((kt + 3) * BK, na, nb);
-    __builtin_amdgcn_sched_barrier(0);   // the copies go out now, not next to the wait for them
-    compute(kt * BK, la, lb);
-  };
-  issue(0, a0, b0);
-  if constexpr (KIND == EpiKind::AccF32) settle_acc<NS>(acc);   // the C tile (and stage 0) have landed
-  if (nk > 1) issue(BK, a1, b1);
-  if (nk > 2) issue(2 * BK, a2, b2);
-  // Whole groups of 4 steps without early exits (an exit between the unrolled
-  // steps makes the register allocator spill), then the remaining 0-3 steps.
-  int kt = 0;
-  for (; kt + 4 <= nk; kt += 4) {
-    step(kt, a0, b0, a3, b3);
-    step(kt + 1, a1, b1, a0, b0);
-    step(kt + 2, a2, b2, a1, b1);
-    step(kt + 3, a3, b3, a2, b2);
-  }
-  const int rest = nk - kt;
-  if (rest > 0) step(kt, a0, b0, a3, b3);
-  if (rest > 1) step(kt + 1, a1, b1, a0, b0);
-  if (rest > 2) step(kt + 2, a2, b2, a1, b1);
-  wait_vm<0>();      // no copy may land in the stages once they are staging space (or after the end)
-  if constexpr (KIND == EpiKind::AccF32) {
-    acc_store_f32<NS>(acc, p, static_cast<float*>(p.epi.c), p.epi.ldc, static_cast<int64_t>(m0) + wm * 128, tn,
-                      ncol, lane);
-  } else {
-    __syncthreads();   // every wave is done reading the stages before they become staging space
-    uint8_t* mine = wave == 0 ? a0 : wave == 1 ? b0 : wave == 2 ? a1 : wave == 3 ? b1 : wave == 4 ? a2
-                  : wave == 5 ? b2 : wave == 6 ? a3 : b3;
-    store_tile<KIND, PAIR, NS>(p, acc, reinterpret_cast<float*>(mine), static_cast<int64_t>(m0) + wm * 128, tn,
-                               ncol, lane);
-  }
-}
-
-// ---------------------------------------------------------- BK = 64 variant
-// Two stages of 64 k (32 KB per operand each, 128 KB in all).  A KC copy
-// instruction moves 8 whole rows of 128 bytes (one cache line each, so no
-// line is fetched twice); an MN copy instruction moves 2 k-rows of 512 bytes.
-// KC slot s of row r holds chunk s ^ ((r >> 1) & 7).  Two rows share a 256-byte
-// bank line (r % 2 picks the half), so the 16 rows one 16-lane group of a
-// fragment read touches cover all 64 banks once.
-constexpr int BK2 = 64;
-constexpr int TILE2 = 256 * BK2 * 2;     // 32 KB per operand per stage
-
-__device__ __forceinline__ int kc2_off(int row, int chunk) { return row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4); }
-
+// ---------------------------------------------------------- 256-row tiles, BK = 64
 template <int WAVES>
 struct Kc2Rows {
   const uint16_t* row[32 / WAVES];
@@ -786,12 +605,13 @@ __device__ __forceinline__ Kc2Rows<WAVES> kc2_rows(const Operand& op, int x0, in
   return r;
 }
 
-template <int WAVES>
-__device__ __forceinline__ void copy2_kc(uint8_t* lds, const Kc2Rows<WAVES>& rows, int k0, int wave) {
+// RAGGED: K may end inside the stage (or before it); chunks past it copy zeros.
+template <int WAVES, bool RAGGED>
+__device__ __forceinline__ void copy2_kc(uint8_t* lds, const Kc2Rows<WAVES>& rows, int k0, int K, int wave) {
   const int k = k0 + rows.c8;
 #pragma unroll
   for (int q = 0; q < 32 / WAVES; ++q)
-    dma16(rows.row[q] + k, lds + (wave + WAVES * q) * 1024);
+    dma16(!RAGGED || k < K ? rows.row[q] + k : zeros(), lds + (wave + WAVES * q) * 1024);
 }
 
 // MN copies.  For an operand whose rows are one plain array (no sequence-
@@ -804,6 +624,46 @@ __device__ __forceinline__ void copy2_kc(uint8_t* lds, const Kc2Rows<WAVES>& row
 // two arms issue textually different copies
 // (dma16<1> for the split one): with identical ones the compiler sinks the copy
 // below the branch and computes both addresses on every copy.
+// How the k-rows of the MN operands map to memory: one plain array; runs of at
+// least 64 rows per stage (plain, or gathered slots of a multiple of 64 rows:
+// one scalar mapping per stage); or any slots (a mapping per lane and copy).  The
+// host picks the kernel, so that a main loop holds only its own mapping.
+constexpr int kPlainRows = 0, kRunRows = 1, kAnyRows = 2;
+
+// The own or the peer pointer, picked by arithmetic on the two values: a select
+// of the members' addresses would put the kernel argument on the stack.
+__device__ __forceinline__ const uint16_t* pick(const RowSrc& src, bool peer) {
+  const uint64_t a = reinterpret_cast<uint64_t>(src.own), b = reinterpret_cast<uint64_t>(src.peer);
+  return reinterpret_cast<const uint16_t*>(a + ((b - a) & (0ull - static_cast<uint64_t>(peer))));
+}
+__device__ __forceinline__ const uint16_t* mapped_row(const RowSrc& src, int k) {
+  if (src.t == 1) return src.own + static_cast<int64_t>(k) * src.ld;
+  const uint32_t o = src.row_index(k);
+  return pick(src, o >> 31) + static_cast<int64_t>(o & 0x7fffffffu) * src.ld;
+}
+// Rows of a stage of a split operand whose slots are no multiple of 64 rows:
+// the sequence of the stage's first row is found once (a scalar division), a
+// lane steps to the next sequence at most once where s_c >= 64.  Rows past the
+// last sequence give addresses that the caller replaces.
+struct StageRows {
+  int b0, i0;
+  __device__ __forceinline__ const uint16_t* row(const RowSrc& src, int kr) const {
+    int bi = b0, i = i0 + kr;
+    while (i >= src.s_c) {
+      i -= src.s_c;
+      ++bi;
+    }
+    const int lo = src.r * src.s_sp;
+    const bool own = i >= lo && i < lo + src.s_sp;
+    const int r = own ? bi * src.s_sp + (i - lo) : bi * (src.t - 1) * src.s_sp + (i < lo ? i : i - src.s_sp);
+    return pick(src, !own) + static_cast<int64_t>(r) * src.ld;
+  }
+};
+__device__ __forceinline__ StageRows stage_rows(const RowSrc& src, int k0) {
+  const int b0 = k0 / src.s_c;
+  return StageRows{b0, k0 - b0 * src.s_c};
+}
+
 struct Mn2Rows {
   uint32_t off0;   // element offset of the lane's 16 bytes for copy 0 at k0 = 0
 };
@@ -811,47 +671,42 @@ struct Mn2Rows {
 template <int WAVES>
 __device__ __forceinline__ Mn2Rows mn2_rows(const Operand& op, int x0, int wave, int lane) {
   const int kr = 2 * wave + (lane >> 5);
-  const int lc = (lane & 31) ^ mn_swz(kr);
+  const int lc = (lane & 31) ^ mn_swz<256>(kr);
   int x = x0 + lc * 8;
   if (x >= op.rows) x = op.rows - 8;
   return Mn2Rows{static_cast<uint32_t>(kr * op.src.ld + x)};
 }
 
-template <int WAVES>
-__device__ __forceinline__ void copy2_mn(uint8_t* lds, const Operand& op, const Mn2Rows& rows, int x0, int k0,
+template <int WAVES, bool RAGGED, int MAP>
+__device__ __forceinline__ void copy2_mn(uint8_t* lds, const Operand& op, const Mn2Rows& rows, int x0, int k0, int K,
                                          int wave, int lane) {
   // A stage's 64 k-rows are consecutive in memory when the operand is one
   // plain array, and also when it is split but every sequence-parallel slot
   // holds a multiple of 64 rows (stages start at multiples of 64, so none
   // straddles a slot or a sequence): then the stage's first row is mapped
   // once (uniform, scalar) and each lane adds its fixed offset.
-  if (op.src.t == 1 || op.src.s_sp % BK2 == 0) {       // uniform
-    const uint16_t* base0;
-    if (op.src.t == 1) {
-      base0 = op.src.own + static_cast<int64_t>(k0) * op.src.ld;
-    } else {
-      // pick own or peer by arithmetic on the two pointer values: a select of
-      // the members' addresses would put the kernel argument on the stack
-      const uint32_t o = op.src.row_index(k0);
-      const uint64_t own = reinterpret_cast<uint64_t>(op.src.own), peer = reinterpret_cast<uint64_t>(op.src.peer);
-      const uint64_t pick = own + ((peer - own) & (0ull - static_cast<uint64_t>(o >> 31)));
-      base0 = reinterpret_cast<const uint16_t*>(pick) + static_cast<int64_t>(o & 0x7fffffffu) * op.src.ld;
-    }
+  if (MAP != kAnyRows || op.src.t == 1 || op.src.s_sp % BK2 == 0) {       // uniform
+    const uint16_t* base0 = MAP != kPlainRows ? mapped_row(op.src, RAGGED && k0 >= K ? 0 : k0)
+                                              : op.src.own + static_cast<int64_t>(k0) * op.src.ld;
 #pragma unroll
-    for (int q = 0; q < 32 / WAVES; ++q)
-      dma16(base0 + static_cast<int64_t>(2 * WAVES * q) * op.src.ld + rows.off0, lds + (wave + WAVES * q) * 1024);
+    for (int q = 0; q < 32 / WAVES; ++q) {
+      const uint16_t* g = base0 + static_cast<int64_t>(2 * WAVES * q) * op.src.ld + rows.off0;
+      if constexpr (RAGGED) g = k0 + 2 * (wave + WAVES * q) + (lane >> 5) < K ? g : zeros();
+      dma16(g, lds + (wave + WAVES * q) * 1024);
+    }
     return;
   }
+  const StageRows sr = stage_rows(op.src, k0);
 #pragma unroll
   for (int q = 0; q < 32 / WAVES; ++q) {
     const int kb = wave + WAVES * q;
     const int kr = 2 * kb + (lane >> 5);
-    const int lc = (lane & 31) ^ mn_swz(kr);
+    const int lc = (lane & 31) ^ mn_swz<256>(kr);
     int x = x0 + lc * 8;
     if (x >= op.rows) x = op.rows - 8;
-    const uint32_t o = op.src.row_index(k0 + kr);
-    const uint16_t* base = (o & 0x80000000u) ? op.src.peer : op.src.own;
-    dma16<1>(base + static_cast<int64_t>(o & 0x7fffffffu) * op.src.ld + x, lds + kb * 1024);
+    const uint16_t* g = sr.row(op.src, kr) + x;
+    if constexpr (RAGGED) g = k0 + kr < K ? g : zeros();
+    dma16<1>(g, lds + kb * 1024);
   }
 }
 
@@ -860,27 +715,17 @@ struct Frags2 {
   bf16x8 a[4], b[NS];
 };
 
-// KC fragment of rows x0 + lane%32 (x0 a multiple of 32), k = 16 kk + 8 (lane/32) + 0..7.
-template <Layout L>
-__device__ __forceinline__ bf16x8 frag2(const uint8_t* lds, int x0, int kk, int lane) {
-  if constexpr (L == Layout::KC) {
-    return *reinterpret_cast<const bf16x8*>(lds + kc2_off(x0 + (lane & 31), 2 * kk + (lane >> 5)));
-  } else {
-    return frag<Layout::MN>(lds, x0, kk, lane);
-  }
-}
-
 // Fragments are read in the order the products consume them (A0, B0 .. B(NS-1),
 // A1, A2, A3), so the first products of the next sub-step wait on the
 // earliest reads.
 template <Layout LA, Layout LB, int NS>
 __device__ __forceinline__ void read_frags2(Frags2<NS>& f, const uint8_t* la, const uint8_t* lb, int wm,
                                             const int* ncol, int kk, int lane) {
-  f.a[0] = frag2<LA>(la, wm * 128, kk, lane);
+  f.a[0] = frag<LA, 256>(la, wm * 128, kk, lane);
 #pragma unroll
-  for (int ns = 0; ns < NS; ++ns) f.b[ns] = frag2<LB>(lb, ncol[ns], kk, lane);
+  for (int ns = 0; ns < NS; ++ns) f.b[ns] = frag<LB, 256>(lb, ncol[ns], kk, lane);
 #pragma unroll
-  for (int ms = 1; ms < 4; ++ms) f.a[ms] = frag2<LA>(la, wm * 128 + ms * 32, kk, lane);
+  for (int ms = 1; ms < 4; ++ms) f.a[ms] = frag<LA, 256>(la, wm * 128 + ms * 32, kk, lane);
 }
 
 template <int NS>
@@ -912,7 +757,7 @@ __device__ __forceinline__ void interleave2() {
 // The BK = 64 main loop of one tile over its stages [kb, kb + n), n even:
 // products added into acc.  The four stage buffers a0 b0 a1 b1 (32 KB each)
 // hold two stages.
-template <Layout LA, Layout LB, int WAVES>
+template <Layout LA, Layout LB, int WAVES, bool RAGGED, int MAP>
 __device__ __forceinline__ void mainloop64(const GemmParams& p, f32x16 (&acc)[4][WAVES == 8 ? 2 : 4], int tm, int tn,
                                            int kb, int n, uint8_t* a0, uint8_t* b0, uint8_t* a1, uint8_t* b1,
                                            int wave, int lane, int wm, const int* ncol) {
@@ -928,13 +773,13 @@ __device__ __forceinline__ void mainloop64(const GemmParams& p, f32x16 (&acc)[4]
   // stage kt of the range (stages past its end repeat the last one: the wait counts stay fixed)
   auto issue_a = [&](int kt, uint8_t* la) {
     const int k0 = (kb + min(kt, n - 1)) * BK2;
-    if constexpr (LA == Layout::KC) copy2_kc<WAVES>(la, ra, k0, wave);
-    else copy2_mn<WAVES>(la, p.A, ma, m0, k0, wave, lane);
+    if constexpr (LA == Layout::KC) copy2_kc<WAVES, RAGGED>(la, ra, k0, p.K, wave);
+    else copy2_mn<WAVES, RAGGED, MAP>(la, p.A, ma, m0, k0, p.K, wave, lane);
   };
   auto issue_b = [&](int kt, uint8_t* lb) {
     const int k0 = (kb + min(kt, n - 1)) * BK2;
-    if constexpr (LB == Layout::KC) copy2_kc<WAVES>(lb, rb, k0, wave);
-    else copy2_mn<WAVES>(lb, p.B, mb, n0, k0, wave, lane);
+    if constexpr (LB == Layout::KC) copy2_kc<WAVES, RAGGED>(lb, rb, k0, p.K, wave);
+    else copy2_mn<WAVES, RAGGED, MAP>(lb, p.B, mb, n0, k0, p.K, wave, lane);
   };
 
   Frags2<NS> f0, f1;
@@ -995,7 +840,7 @@ __device__ __forceinline__ float* stage_space(uint8_t* a0, uint8_t* b0, uint8_t*
   return reinterpret_cast<float*>(mine);
 }
 
-template <Layout LA, Layout LB, EpiKind KIND, int PAIR, int WAVES>
+template <Layout LA, Layout LB, EpiKind KIND, int PAIR, int WAVES, bool RAGGED, int MAP>
 __global__ void __launch_bounds__(WAVES * 64, 1) gemm_bk64(GemmParams p) {
   constexpr int NS = WAVES == 8 ? 2 : 4;
   __shared__ __attribute__((aligned(16))) uint8_t a0[TILE2], b0[TILE2], a1[TILE2], b1[TILE2];
@@ -1018,7 +863,8 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemm_bk64(GemmParams p) {
     ncol[j] = lo_col<WAVES, PAIR>(wn, j);
     ncol[j + NS / 2] = ncol[j] + PAIR;
   }
-  const int n_st = p.K / BK2 / parts;          // stages per part (the host keeps it even)
+  // stages per part, even; past the end of K they hold zeros (only without a split)
+  const int n_st = RAGGED ? (p.K + 2 * BK2 - 1) / (2 * BK2) * 2 : p.K / BK2 / parts;
   float* cbase = nullptr;
   int64_t ldc = 0;
   if constexpr (KIND == EpiKind::AccF32) {
@@ -1035,8 +881,8 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemm_bk64(GemmParams p) {
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < NS; ++j) acc[i][j] = f32x16{};
-  // K is a multiple of 2 * BK2 * parts (the host picks this kernel only then).
-  mainloop64<LA, LB, WAVES>(p, acc, tm, tn, part * n_st, n_st, a0, b0, a1, b1, wave, lane, wm, ncol);
+  // Unless RAGGED, K is a multiple of 2 * BK2 * parts.
+  mainloop64<LA, LB, WAVES, RAGGED, MAP>(p, acc, tm, tn, part * n_st, n_st, a0, b0, a1, b1, wave, lane, wm, ncol);
   // The fp32 accumulate: the products start from zero and part 0 adds the C
   // tile in the epilogue, whose loads overlap its stores (loading C into the
   // accumulators before the first product measured 2-3% slower on the largest
@@ -1054,34 +900,377 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemm_bk64(GemmParams p) {
   }
 }
 
-// Kernel choice: K a multiple of 128 (and every K split) takes the 8-wave
-// BK = 64 kernel, the fastest on the Llama layer shapes; any other K the
-// BK = 32 kernel, whose copies mask the ragged end of K.
-template <Layout LA, Layout LB, EpiKind KIND, int PAIR>
-hipError_t launch(const GemmParams& p, hipStream_t stream) {
+// ---------------------------------------------------------- T-row tiles, T = 128 or 64
+// For grids that 256-row tiles would leave mostly empty: with one workgroup per
+// CU or less, a 256-row stage costs about 1.1 us (copy latency, LDS latency and
+// barrier in turn), whatever the chip does elsewhere.  A workgroup owns a
+// T x T tile: W / 4 groups of 4 waves, each wave a quarter of the tile (2 x 2
+// MFMA blocks at T = 128, one at T = 64) over its group's share of every
+// stage's k; with W = 8 the two groups' sums meet in the epilogue.  Operands
+// stream through a ring of S stages of 64 k with S - 1 of them in flight: a
+// tile's time is the copy latency plus its products, where the 256-row kernel's
+// two stages expose the latency when few workgroups run.  One barrier per stage;
+// at a full chip the copies bound it (T = 128: 32 KB per stage in 0.6 us, 14 TB/s
+// over the chip).  Layer of hidden 1024 on 1000 tokens, forward + backward: 690 ->
+// 347 us; hidden 256 on 128 tokens: 317 -> 125 us (all GEMMs on 256-row tiles
+// before).
+// W = 8 (two waves per SIMD), S = 128 KB of stages: one workgroup per CU, for
+// grids that fit the chip once.  W = 4 with 64 KB of stages: two workgroups per
+// CU, for larger grids.
+//
+// Columns: the tile's T/2 "low" columns j = tn T/2 + (0..T/2) and their partners
+// `pair` further, low column j sitting at matrix column (j / pair) 2 pair +
+// j % pair.  With pair = T/2 that is T consecutive columns; with pair = d_h/2 it
+// keeps RoPE pairs together and with pair = f the gate and up columns, for any T.
+//
+// A wave issues C = T / (8 W) copies of 1 KB per operand and stage.
+template <int T, int W>
+struct RowPtrs {
+  const uint16_t* row[T / (8 * W)];
+  int c8;
+};
+
+// Source rows of the wave's copies of a KC stage: copy q moves tile rows
+// 8 (wave + W q) + lane/8.
+template <int T, int W, bool PAIRED>
+__device__ __forceinline__ RowPtrs<T, W> tile_rows(const Operand& op, int tile, int pair, int wave, int lane) {
+  RowPtrs<T, W> r;
+  r.c8 = 8 * ((lane & 7) ^ (4 * (wave & 1) + (lane >> 4)));
+#pragma unroll
+  for (int q = 0; q < T / (8 * W); ++q) {
+    const int xr = 8 * (wave + W * q) + (lane >> 3);
+    int gx = tile * T + xr;
+    if constexpr (PAIRED) {
+      const int j = tile * (T / 2) + (xr & (T / 2 - 1));
+      gx = j / pair * 2 * pair + j % pair + (xr >= T / 2 ? pair : 0);
+    }
+    r.row[q] = op.src.row(min(gx, op.rows - 1));
+  }
+  return r;
+}
+
+// The source addresses of the wave's copies of a stage are formed ahead of the
+// barrier that frees the stage's slot, under the products; the copies then go
+// out between the products that follow the barrier.
+template <int C>
+struct StageSrc {
+  const uint16_t* g[C];
+};
+template <int T, int W>
+__device__ __forceinline__ StageSrc<T / (8 * W)> tile_src_kc(const RowPtrs<T, W>& rows, int k0, int K) {
+  StageSrc<T / (8 * W)> r;
+  const int k = k0 + rows.c8;
+#pragma unroll
+  for (int q = 0; q < T / (8 * W); ++q) r.g[q] = k < K ? rows.row[q] + k : zeros();
+  return r;
+}
+
+// MN stage: an instruction moves 512 / T k-rows of T columns; a lane's offset
+// in its stage is the same for every copy up to a uniform stride, as in
+// copy2_mn (the swizzle depends on k-row bits that the copies do not change).
+template <int T>
+__device__ __forceinline__ uint32_t tile_lane_off(const Operand& op, int x0, int wave, int lane) {
+  constexpr int LPR = T / 8, RPI = 64 / LPR;      // lanes per k-row, k-rows per instruction
+  const int kr = RPI * wave + lane / LPR;
+  return static_cast<uint32_t>(kr * op.src.ld + min(x0 + ((lane % LPR) ^ mn_swz<T>(kr)) * 8, op.rows - 8));
+}
+template <int T, int W, int MAP>
+__device__ __forceinline__ StageSrc<T / (8 * W)> tile_src_mn(const Operand& op, uint32_t off, int x0, int k0, int K,
+                                                             int wave, int lane) {
+  constexpr int LPR = T / 8, RPI = 64 / LPR, C = T / (8 * W);
+  StageSrc<C> r;
+  if (MAP != kAnyRows || op.src.t == 1 || op.src.s_sp % BK2 == 0) {   // uniform: the stage is one run of rows (see copy2_mn)
+    const uint16_t* base0 = (MAP != kPlainRows ? mapped_row(op.src, min(k0, K - 1))
+                                               : op.src.own + static_cast<int64_t>(k0) * op.src.ld) + off;
+#pragma unroll
+    for (int q = 0; q < C; ++q) {
+      const uint16_t* g = base0 + static_cast<int64_t>(W * RPI * q) * op.src.ld;
+      r.g[q] = k0 + RPI * (wave + W * q) + lane / LPR < K ? g : zeros();
+    }
+    return r;
+  }
+  const StageRows sr = stage_rows(op.src, k0);
+#pragma unroll
+  for (int q = 0; q < C; ++q) {
+    const int kr = RPI * (wave + W * q) + lane / LPR;
+    const int x = min(x0 + ((lane % LPR) ^ mn_swz<T>(kr)) * 8, op.rows - 8);
+    r.g[q] = k0 + kr < K ? sr.row(op.src, kr) + x : zeros();
+  }
+  return r;
+}
+
+template <int N>
+__device__ __forceinline__ void wait_copies() {
+  static_assert(N <= 63, "the wait counter holds 6 bits");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+template <Layout LA, Layout LB, EpiKind KIND, int T, int W, int S, int MAP>
+__global__ void __launch_bounds__(W * 64) gemm_tile(GemmParams p) {
+  constexpr int OPB = T * BK2 * 2, STB = 2 * OPB;   // bytes per operand and per stage
+  constexpr int R = T / 64;                         // 32-row blocks per wave and operand
+  constexpr int C = T / (8 * W), PER = 2 * C;       // copies per wave, per operand and per stage
+  constexpr int KS = 2, NSUB = BK2 / 16 / (W / 4) / KS;   // a wave's share of a stage: NSUB sub-steps of KS 16-k products
+  constexpr int NACC = T == 64 ? 2 : 1;             // T = 64: two chains, so that no product waits for the one before it
+  constexpr bool PAIRED = KIND == EpiKind::QkvRope || KIND == EpiKind::SwiGLUFwd;
+  static_assert(S * STB >= T * T * 4, "the tile is staged in the ring");
+  __shared__ __attribute__((aligned(16))) uint8_t ring[S * STB];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+
+  const int parts = p.k_splits > 1 ? p.k_splits : 1;
+  const int tiles_m = (p.M + T - 1) / T, tiles_n = (p.N + T - 1) / T, tiles = tiles_m * tiles_n;
+  const int pid_all = xcd_remap(blockIdx.x, gridDim.x);
+  const int part = pid_all / tiles, pid = pid_all - part * tiles;
+  constexpr int GM = GROUP_M * BM / T;              // the same rows of C per group as the 256-row kernel
+  const int first_m = pid / (GM * tiles_n) * GM, gm = min(tiles_m - first_m, GM);
+  const int tm = first_m + pid % (GM * tiles_n) % gm, tn = pid % (GM * tiles_n) / gm;
+  const int pair = PAIRED ? p.pair : T / 2;
+
+  const int all_st = (p.K + BK2 - 1) / BK2;
+  const int per_part = (all_st + parts - 1) / parts;
+  const int st0 = part * per_part, n = min(per_part, all_st - st0);   // the last part may be shorter (or empty)
+
+  RowPtrs<T, W> ra{}, rb{};
+  uint32_t oa = 0, ob = 0;
+  if constexpr (LA == Layout::KC) ra = tile_rows<T, W, false>(p.A, tm, pair, wave, lane);
+  else oa = tile_lane_off<T>(p.A, tm * T, wave, lane);
+  if constexpr (LB == Layout::KC) rb = tile_rows<T, W, PAIRED>(p.B, tn, pair, wave, lane);
+  else ob = tile_lane_off<T>(p.B, tn * T, wave, lane);
+  const uint32_t ring_addr = lds_addr(ring) + wave * 1024;
+  StageSrc<C> ga, gb;
+  auto prepare = [&](int st) __attribute__((always_inline)) {
+    const int k0 = (st0 + st) * BK2;
+    if constexpr (LA == Layout::KC) ga = tile_src_kc<T, W>(ra, k0, p.K);
+    else ga = tile_src_mn<T, W, MAP>(p.A, oa, tm * T, k0, p.K, wave, lane);
+    if constexpr (LB == Layout::KC) gb = tile_src_kc<T, W>(rb, k0, p.K);
+    else gb = tile_src_mn<T, W, MAP>(p.B, ob, tn * T, k0, p.K, wave, lane);
+  };
+  auto fire = [&](int c, int slot) __attribute__((always_inline)) {   // copy c of the prepared stage
+    dma16(c < C ? ga.g[c % C] : gb.g[c % C], ring_addr + slot * STB + (c < C ? 0 : OPB) + c % C * (W * 1024));
+  };
+
+  f32x16 acc[NACC][R][R];
+#pragma unroll
+  for (int c = 0; c < NACC; ++c)
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int j = 0; j < R; ++j) acc[c][i][j] = f32x16{};
+
+  struct Frags {
+    bf16x8 a[KS][R], b[KS][R];
+  };
+  auto read = [&](Frags& f, int slot, int sub) __attribute__((always_inline)) {
+    const uint8_t* la = ring + slot * STB;
+#pragma unroll
+    for (int q = 0; q < KS; ++q)
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        f.a[q][i] = frag<LA, T>(la, wm * (T / 2) + 32 * i, (kg * NSUB + sub) * KS + q, lane);
+        f.b[q][i] = frag<LB, T>(la + OPB, wn * (T / 2) + 32 * i, (kg * NSUB + sub) * KS + q, lane);
+      }
+  };
+  // The products of one sub-step, the LDS reads of the next one going out between the first of them.
+  auto products = [&](const Frags& f) __attribute__((always_inline)) {
+    constexpr int NM = KS * R * R;
+    constexpr int DS = KS * R * ((LA == Layout::KC ? 1 : 2) + (LB == Layout::KC ? 1 : 2));
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      const int q = m / (R * R), i = m / R % R, j = m % R;
+      acc[q % NACC][i][j] =
+          __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[q][i], f.b[q][j], acc[q % NACC][i][j], 0, 0, 0);
+    }
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (m < NM / 2) __builtin_amdgcn_sched_group_barrier(0x100, DS * 2 / NM, 0);
+    }
+  };
+  // Stages past the last one are copied too (their k is past the part's end or
+  // past K, and nothing uses them), so that the number in flight is fixed.
+#pragma unroll
+  for (int st = 0; st < S; ++st) {
+    prepare(st);
+#pragma unroll
+    for (int c = 0; c < PER; ++c) fire(c, st);
+  }
+  wait_copies<(S - 1) * PER>();
+  stage_barrier();
+  Frags f0, f1;
+  read(f0, 0, 0);
+  int slot = 0;
+  // Ends stage st: publishes the next stage and starts reading it into nxt, runs
+  // the products of cur (the stage's last sub-step), and refills the freed slot.
+  auto turn = [&](int st, const Frags& cur, Frags& nxt) __attribute__((always_inline)) {
+    wait_copies<(S - 2) * PER>();
+    stage_barrier();                    // stage st + 1 is visible, and every wave has read all of stage st
+    const int next = slot + 1 == S ? 0 : slot + 1;
+    read(nxt, next, 0);
+    products(cur);
+#pragma unroll
+    for (int c = 0; c < PER; ++c) fire(c, slot);
+    slot = next;
+  };
+  if constexpr (NSUB == 2) {
+    for (int st = 0; st < n; ++st) {
+      prepare(st + S);
+      read(f1, slot, 1);
+      products(f0);
+      turn(st, f1, f0);
+    }
+  } else {
+    int st = 0;
+    for (; st + 2 <= n; st += 2) {
+      prepare(st + S);
+      turn(st, f0, f1);
+      prepare(st + 1 + S);
+      turn(st + 1, f1, f0);
+    }
+    if (st < n) {
+      prepare(st + S);
+      turn(st, f0, f1);
+    }
+  }
+  wait_copies<0>();   // no copy may land in the ring once it is staging space
+
+  // Epilogue: the tile goes through LDS (columns of rows with bit 2 set moved by
+  // 32, so that the two half-waves write different banks), then every thread
+  // takes 8-column vectors of the low half with their partners.
+  constexpr int VPR = T / 16, ITERS = T * VPR / (W * 64) > 0 ? T * VPR / (W * 64) : 1;
+  const bool has_vec = T * VPR >= W * 64 || tid < T * VPR;
+  float* stg = reinterpret_cast<float*>(ring);
+  constexpr bool kSplit = KIND == EpiKind::AccF32 || KIND == EpiKind::StoreBF16;
+  const bool to_partial = kSplit && (KIND == EpiKind::AccF32 ? part > 0 : parts > 1);
+  auto column = [&](int v) {
+    const int j = tn * (T / 2) + 8 * v;
+    return PAIRED ? j / pair * 2 * pair + j % pair : tn * T + 8 * v;
+  };
+  EpiIn<KIND> in[ITERS];
+  if (!to_partial && has_vec) {
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) {
+      const int idx = it * (W * 64) + tid;
+      epi_load<KIND>(p, tm * T + idx / VPR, column(idx % VPR), pair, in[it]);
+    }
+  }
+  __syncthreads();    // every wave is done reading the ring
+  auto stage_acc = [&](bool add) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int r = wm * (T / 2) + 32 * i + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+          const int c = wn * (T / 2) + 32 * j + (lane & 31);
+          float* d = stg + r * T + (c ^ (((r >> 2) & 1) << 5));
+          float v = acc[0][i][j][e];
+          if constexpr (NACC == 2) v += acc[1][i][j][e];
+          *d = add ? *d + v : v;
+        }
+  };
+  if (kg == 0) stage_acc(false);
+  __syncthreads();
+  if constexpr (W == 8) {             // the second k group adds its sums
+    if (kg == 1) stage_acc(true);
+    __syncthreads();
+  }
+  if (!has_vec) return;
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it) {
+    const int idx = it * (W * 64) + tid;
+    const int r = idx / VPR, v = idx % VPR;
+    const int64_t m = static_cast<int64_t>(tm) * T + r;
+    const int flip = ((r >> 2) & 1) << 5;
+    const float4* lo4 = reinterpret_cast<const float4*>(stg + r * T + ((8 * v) ^ flip));
+    const float4* hi4 = reinterpret_cast<const float4*>(stg + r * T + ((T / 2 + 8 * v) ^ flip));
+    const float4 l0 = lo4[0], l1 = lo4[1], h0 = hi4[0], h1 = hi4[1];
+    if (to_partial) {
+      if (m >= p.M) continue;
+      float* c = p.partial + (static_cast<int64_t>(KIND == EpiKind::AccF32 ? part - 1 : part) * p.M + m) * p.N;
+      const int nlo = column(v), nhi = nlo + pair;
+      if (nlo < p.N) {
+        reinterpret_cast<float4*>(c + nlo)[0] = l0;
+        reinterpret_cast<float4*>(c + nlo)[1] = l1;
+      }
+      if (nhi < p.N) {
+        reinterpret_cast<float4*>(c + nhi)[0] = h0;
+        reinterpret_cast<float4*>(c + nhi)[1] = h1;
+      }
+      continue;
+    }
+    float lo[8] = {l0.x, l0.y, l0.z, l0.w, l1.x, l1.y, l1.z, l1.w};
+    float hi[8] = {h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w};
+    epilogue<KIND>(p, m, column(v), pair, lo, hi, in[it]);
+  }
+}
+
+template <Layout LA, Layout LB, EpiKind KIND, int T, int W, int S, int MAP>
+hipError_t launch_tile(const GemmParams& p, hipStream_t stream) {
+  const int parts = p.k_splits > 1 ? p.k_splits : 1;
+  const unsigned tiles = static_cast<unsigned>((p.M + T - 1) / T) * ((p.N + T - 1) / T);
+  hipLaunchKernelGGL((gemm_tile<LA, LB, KIND, T, W, S, MAP>), dim3(tiles * parts), dim3(W * 64), 0, stream, p);
+  return hipGetLastError();
+}
+
+// Tile size and split: see gemm_plan.
+template <Layout LA, Layout LB, EpiKind KIND, int MAP>
+hipError_t launch_small(const GemmParams& p, hipStream_t stream) {
+  const int T = p.tile, parts = p.k_splits > 1 ? p.k_splits : 1;
+  const int64_t blocks = static_cast<int64_t>((p.M + T - 1) / T) * ((p.N + T - 1) / T) * parts;
+  if (T == 128)
+    return blocks <= 256 ? launch_tile<LA, LB, KIND, 128, 8, 4, MAP>(p, stream)
+                         : launch_tile<LA, LB, KIND, 128, 4, 2, MAP>(p, stream);
+  return blocks <= 256 ? launch_tile<LA, LB, KIND, 64, 8, 8, MAP>(p, stream)
+                       : launch_tile<LA, LB, KIND, 64, 4, 4, MAP>(p, stream);
+}
+template <Layout LA, Layout LB, EpiKind KIND, int PAIR, int MAP>
+hipError_t launch256(const GemmParams& p, hipStream_t stream) {
+  const int parts = p.k_splits > 1 ? p.k_splits : 1;
   const int tiles_m = (p.M + BM - 1) / BM;
   const int tiles_n = p.B.split_rows ? (p.B.split_rows + 127) / 128 : (p.N + BN - 1) / BN;
-  const int parts = p.k_splits > 1 ? p.k_splits : 1;
-  if (parts > 1 && ((KIND != EpiKind::AccF32 && KIND != EpiKind::StoreBF16) || p.K % (2 * BK2 * parts) != 0 ||
-                    !p.partial))
-    return hipErrorInvalidValue;
+  if (parts > 1 && p.K % (2 * BK2 * parts) != 0) return hipErrorInvalidValue;
   // the fp32 accumulate's whole-tile epilogue addresses 128 rows of C with 32-bit byte offsets
   if (KIND == EpiKind::AccF32 && p.epi.ldc > (int64_t{1} << 21)) return hipErrorInvalidValue;
   const dim3 grid(tiles_m * tiles_n * parts);
   if (p.K % (2 * BK2) == 0)
-    hipLaunchKernelGGL((gemm_bk64<LA, LB, KIND, PAIR, 8>), grid, dim3(512), 0, stream, p);
+    hipLaunchKernelGGL((gemm_bk64<LA, LB, KIND, PAIR, 8, false, MAP>), grid, dim3(512), 0, stream, p);
   else
-    hipLaunchKernelGGL((gemm_bk32<LA, LB, KIND, PAIR>), grid, dim3(512), 0, stream, p);
+    hipLaunchKernelGGL((gemm_bk64<LA, LB, KIND, PAIR, 8, true, MAP>), grid, dim3(512), 0, stream, p);
   return hipGetLastError();
+}
+template <Layout LA, Layout LB, EpiKind KIND, int PAIR>
+hipError_t launch(const GemmParams& p, hipStream_t stream) {
+  if (p.k_splits > 1 && ((KIND != EpiKind::AccF32 && KIND != EpiKind::StoreBF16) || !p.partial))
+    return hipErrorInvalidValue;
+  const RowSrc &a = p.A.src, &b = p.B.src;
+  const bool plain = (LA == Layout::KC || a.t == 1) && (LB == Layout::KC || b.t == 1);
+  const bool small = p.tile == 128 || p.tile == 64;
+  if constexpr (LA == Layout::MN) {            // the weight gradients: gathered activations as MN operands
+    const bool runs = (a.t == 1 || a.s_sp % BK2 == 0) && (b.t == 1 || b.s_sp % BK2 == 0);
+    if (small)
+      return plain ? launch_small<LA, LB, KIND, kPlainRows>(p, stream) : launch_small<LA, LB, KIND, kAnyRows>(p, stream);
+    return plain  ? launch256<LA, LB, KIND, PAIR, kPlainRows>(p, stream)
+           : runs ? launch256<LA, LB, KIND, PAIR, kRunRows>(p, stream)
+                  : launch256<LA, LB, KIND, PAIR, kAnyRows>(p, stream);
+  }
+  if (!plain) return hipErrorInvalidValue;     // every other MN operand is a weight
+  // kRunRows maps a plain array too; on the dX GEMMs of full chips its main loop
+  // measured 2-3% faster than the shorter one of kPlainRows
+  return small ? launch_small<LA, LB, KIND, kPlainRows>(p, stream) : launch256<LA, LB, KIND, PAIR, kRunRows>(p, stream);
 }
 
 }  // namespace
 
-hipError_t gemm(const GemmParams& p, Layout la, Layout lb, hipStream_t stream) {
-  if (p.M <= 0 || p.N <= 0 || p.K <= 0) return hipSuccess;
+hipError_t gemm(const GemmParams& params, Layout la, Layout lb, hipStream_t stream) {
+  if (params.M <= 0 || params.N <= 0 || params.K <= 0) return hipSuccess;
   using L = Layout;
   using E = EpiKind;
-  const E k = p.epi.kind;
+  const E k = params.epi.kind;
+  GemmParams p = params;
+  p.pair = k == E::QkvRope ? p.epi.d_h / 2 : k == E::SwiGLUFwd ? p.epi.f : 0;
   if (la == L::KC && lb == L::KC) {
     if (k == E::QkvRope && p.epi.d_h == 128) return launch<L::KC, L::KC, E::QkvRope, 64>(p, stream);
     if (k == E::QkvRope && p.epi.d_h == 64) return launch<L::KC, L::KC, E::QkvRope, 32>(p, stream);
@@ -1155,15 +1344,11 @@ hipError_t gemm_split_store(uint16_t* c, int64_t ldc, const float* partial, int6
   return hipGetLastError();
 }
 
-int gemm_ksplits(int64_t M, int64_t N, int64_t K, bool acc_f32) {
+int gemm_max_splits(int64_t M, int64_t N, int64_t K, bool acc_f32) {
   // Model: a wave of 256 tiles of full K takes T = 2*256*256*K / (1 PFLOP/s / 256 CUs);
   // s parts take ceil(tiles*s / 256) waves of T/s, plus writing and reading the
   // fp32 partials at about 4 TB/s (s - 1 of them when part 0 accumulates into an
   // fp32 C, all s when the result is stored as bf16).  Pick the cheapest s of 1..4.
-  // The rate is deliberately low: the chip is power-limited, so a wave that
-  // leaves CUs idle runs at a higher clock than tile counting suggests (the
-  // 160-tile qkv weight gradient of the 70B shard was no faster in 4 parts),
-  // and only clearly under-filled grids (128 tiles) split.
   const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
   const double t_wave = 2.0 * BM * BN * static_cast<double>(K) / (1e15 / 256.0);
   int best = 1;
@@ -1177,6 +1362,54 @@ int gemm_ksplits(int64_t M, int64_t N, int64_t K, bool acc_f32) {
       best_t = t;
       best = s;
     }
+  }
+  return best;
+}
+
+namespace {
+// Microseconds of a grid of T-row tiles, `st` stages of 64 k each, on a kernel
+// that keeps `slots` workgroups on the chip: per round of workgroups a fixed
+// part (launch or drain, first copies), the tile's share of C traffic at 4.8
+// TB/s and c0 + c1 fill per stage, where fill is the part of the slots in use
+// (an emptier chip clocks higher and waits less for memory).
+double grid_us(int64_t tiles, int64_t st, int T, int slots, double fixed, double c0, double c1) {
+  const double c_us = static_cast<double>(slots) * T * T * 8.0 / 4.8e6;
+  const auto round = [&](double fill) { return fixed + fill * c_us + st * (c0 + c1 * fill); };
+  const int64_t full = tiles / slots, rest = tiles % slots;
+  return full * round(1.0) + (rest ? round(static_cast<double>(rest) / slots) : 0.0);
+}
+}  // namespace
+
+// The constants of grid_us are fits to GEMMs of 128 to 8192 rows, 256 to 32064
+// columns and K 128 to 32000 timed in every form on one MI355X (per 64-k stage:
+// 256-row tiles 1.0 us nearly alone, 1.65-1.8 on a full chip; 128-row tiles one
+// per CU 0.37 / 0.6, two per CU 1.1 for both; 64-row tiles one per CU 0.17 /
+// 0.2, two 0.52), within about 15% of the times: e.g. M 2048 N 2048 K 5464
+// K-contiguous 125 us with 64 tiles of 256 rows, 60 with 256 of 128; M 600 N
+// 1280 K 8192 143 / 52 / 27 us with tiles of 256 / 128 / 64; M 4000 N 7168 K
+// 4096 210 / 249 / 402; M 512 N 4096 K 32000 605 in one part and 317 in two
+// with 256-row tiles, 274 and 161 with 128-row ones.
+GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, EpiKind kind, int max_splits) {
+  const bool acc = kind == EpiKind::AccF32;
+  const int64_t stages = (K + BK2 - 1) / BK2;
+  const auto tiles = [&](int64_t T) { return (M + T - 1) / T * ((N + T - 1) / T); };
+  GemmPlan best{256, 1};
+  double best_us = 1e30;
+  for (int s = 1; s <= max_splits; ++s) {
+    if (s > 1 && (N % 4 != 0 || stages < 4 * s)) break;
+    const int n_part = s == 1 ? 0 : (acc ? s - 1 : s);
+    const double reduce = s == 1 ? 0.0 : 4.0 + n_part * 8.0 * static_cast<double>(M) * N / 4e6;
+    const int64_t st = (stages + s - 1) / s;
+    const auto offer = [&](int T, double us) {
+      if (us + reduce < 0.97 * best_us) {
+        best = GemmPlan{T, s};
+        best_us = us + reduce;
+      }
+    };
+    if (s == 1 || K % (2 * BK2 * s) == 0) offer(256, grid_us(tiles(256) * s, (st + 1) / 2 * 2, 256, 256, 8.0, 1.0, 0.65));
+    const int64_t t128 = tiles(128) * s, t64 = tiles(64) * s;
+    offer(128, t128 <= 256 ? grid_us(t128, st, 128, 256, 5.0, 0.33, 0.27) : grid_us(t128, st, 128, 512, 5.0, 0.25, 0.85));
+    offer(64, t64 <= 256 ? grid_us(t64, st, 64, 256, 4.0, 0.15, 0.06) : grid_us(t64, st, 64, 512, 4.0, 0.20, 0.32));
   }
   return best;
 }

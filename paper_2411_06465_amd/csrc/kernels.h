@@ -96,6 +96,8 @@ struct GemmParams {
   int32_t M, N, K;
   Operand A, B;
   EpiParams epi;
+  int32_t tile;                // rows of the kernel's square tile: 256, 128 or 64 (0 = 256)
+  int32_t pair;                // distance of the epilogue's column pairs (QkvRope: d_h/2, SwiGLUFwd: f), set by gemm()
   // AccF32 and StoreBF16 only: the K range is cut into k_splits equal parts
   // (0 or 1 = none).  AccF32: part 0 accumulates into C; part s > 0 stores its
   // fp32 sum to partial + (s - 1) M N (row-major, ld N), which
@@ -106,9 +108,15 @@ struct GemmParams {
 };
 
 hipError_t gemm(const GemmParams& p, Layout la, Layout lb, hipStream_t stream);
-// Parts the K range of an fp32-accumulate GEMM is cut into when one tile per
-// workgroup would leave much of the chip idle (1 = no split).
-int gemm_ksplits(int64_t M, int64_t N, int64_t K, bool acc_f32);
+// The tile size of a GEMM and the parts its K range is cut into: at most
+// max_splits (1 = none; only AccF32 and StoreBF16 can split, into a workspace of
+// splits - 1, for StoreBF16 splits, fp32 M x N partials).
+struct GemmPlan {
+  int32_t tile, splits;
+};
+GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, EpiKind kind, int max_splits);
+// The largest split the layer's workspace is planned for (1 = none).
+int gemm_max_splits(int64_t M, int64_t N, int64_t K, bool acc_f32);
 // C[m][n] += sum over s of partial[s][m][n], s = 0 .. splits - 2, in that order.
 hipError_t gemm_split_reduce(float* c, int64_t ldc, const float* partial, int64_t M, int64_t N, int32_t splits,
                              hipStream_t stream);
@@ -231,11 +239,6 @@ hipError_t xent_grad(const float* probs, int64_t n, int32_t v_t, int64_t v0, con
 hipError_t embed_fwd(const int64_t* ids, const uint16_t* w, int64_t v0, int32_t v_t, int32_t h, int64_t rows,
                      int32_t s_c, int32_t s_sp, int32_t r, int32_t t, const uint16_t* receipt, uint16_t* own,
                      uint16_t* send, hipStream_t stream);
-// Rows of an fp32 [rows][h] sum over the gathered view: own SP rows ->
-// bf16(sum + receipt) into own (receipt may be null), the peers' rows ->
-// bf16(sum) into send (row mapping as RowSrc).
-hipError_t sp_finish(const float* sum, int32_t h, int64_t rows, int32_t s_c, int32_t s_sp, int32_t r, int32_t t,
-                     const uint16_t* receipt, uint16_t* own, uint16_t* send, hipStream_t stream);
 // dw[ids[m] - v0] += dy.row(m) for the ids in range (fp32 atomics).
 hipError_t embed_bwd(const int64_t* ids, RowSrc dy, int64_t v0, int32_t v_t, int32_t h, int64_t rows, float* dw,
                      hipStream_t stream);
