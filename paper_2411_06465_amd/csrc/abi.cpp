@@ -1154,12 +1154,11 @@ extern "C" int embedding_fwd(const l4d_model* m, const l4d_parallel* p, const in
   l4d_stash* st = nullptr;
   if ((rc = stash_reserve_sized(A, x, kEmbStash, L4D_EMB_COUNT, bytes, -1, &st))) return rc;
   auto body = [&]() -> int {
-    HIP_TRY(hipMemcpyAsync(sptr<void>(st, L4D_EMB_IDS), ids, bytes[0], hipMemcpyDeviceToDevice, s));
     return launch("embed_fwd", s, [&] {
       return embed_fwd(ids, static_cast<const uint16_t*>(w_emb), v0, (int32_t)v_t, (int32_t)x.h, x.b * x.s_c,
                        (int32_t)x.s_c, (int32_t)x.s_sp, (int32_t)x.tr, (int32_t)x.t,
                        static_cast<const uint16_t*>(receipt), static_cast<uint16_t*>(x_out),
-                       static_cast<uint16_t*>(send), s);
+                       static_cast<uint16_t*>(send), sptr<int64_t>(st, L4D_EMB_IDS), s);
     });
   };
   if ((rc = body())) {
@@ -1182,7 +1181,7 @@ extern "C" int embedding_bwd(const l4d_model* m, const l4d_parallel* p, l4d_stas
   if ((x.t > 1) != (peer_dx != nullptr)) return fail(L4D_EINVAL, "peer_dx is required iff tp > 1");
   hipStream_t s = static_cast<hipStream_t>(stream_ptr);
   if ((rc = launch("embed_bwd", s, [&] {
-         return embed_bwd(sptr<const int64_t>(st, L4D_EMB_IDS), gathered(dx, peer_dx, x), v0, (int32_t)v_t,
+         return embed_bwd(sptr<int64_t>(st, L4D_EMB_IDS), gathered(dx, peer_dx, x), v0, (int32_t)v_t,
                           (int32_t)x.h, x.b * x.s_c, d_w_emb, s);
        })))
     return rc;

@@ -235,12 +235,13 @@ hipError_t xent_grad(const float* probs, int64_t n, int32_t v_t, int64_t v0, con
 
 // Gathered row m (0 <= m < rows = b*s_c) of the vocabulary-parallel lookup:
 // w[ids[m] - v0] if in [0, v_t) else 0; own SP rows -> own (+ receipt), the
-// peers' rows -> send (row mapping as RowSrc).
+// peers' rows -> send (row mapping as RowSrc); the ids are copied to kept.
 hipError_t embed_fwd(const int64_t* ids, const uint16_t* w, int64_t v0, int32_t v_t, int32_t h, int64_t rows,
                      int32_t s_c, int32_t s_sp, int32_t r, int32_t t, const uint16_t* receipt, uint16_t* own,
-                     uint16_t* send, hipStream_t stream);
-// dw[ids[m] - v0] += dy.row(m) for the ids in range (fp32 atomics).
-hipError_t embed_bwd(const int64_t* ids, RowSrc dy, int64_t v0, int32_t v_t, int32_t h, int64_t rows, float* dw,
+                     uint16_t* send, int64_t* kept, hipStream_t stream);
+// dw[ids[m] - v0] += dy.row(m) for the ids in range (fp32 atomics).  ids is
+// overwritten (sorted in place).
+hipError_t embed_bwd(int64_t* ids, RowSrc dy, int64_t v0, int32_t v_t, int32_t h, int64_t rows, float* dw,
                      hipStream_t stream);
 
 // ---------------------------------------------------------------- optimizer

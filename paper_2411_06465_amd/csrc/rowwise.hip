@@ -552,11 +552,13 @@ __global__ void __launch_bounds__(256) embed_fwd_kernel(const int64_t* __restric
                                                        const uint16_t* __restrict__ w, int64_t v0, int32_t v_t,
                                                        int32_t h, int64_t rows, SpRows sp,
                                                        const uint16_t* __restrict__ receipt,
-                                                       uint16_t* __restrict__ own, uint16_t* __restrict__ send) {
+                                                       uint16_t* __restrict__ own, uint16_t* __restrict__ send,
+                                                       int64_t* __restrict__ kept) {
   const int lane = threadIdx.x & 63;
   const int64_t m = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
   if (m >= rows) return;
-  const int64_t j = ids[m] - v0;
+  const int64_t id = ids[m], j = id - v0;
+  if (lane == 0) kept[m] = id;          // the backward's copy of the ids
   const bool hit = j >= 0 && j < v_t;
   const uint32_t o = sp.map(m);
   const bool mine = !(o & 0x80000000u);
@@ -580,23 +582,106 @@ __global__ void __launch_bounds__(256) embed_fwd_kernel(const int64_t* __restric
   }
 }
 
-// One wave per gathered row whose id is in range: dW[id - v0] += dY[row]
-// (fp32 atomic adds: rows that share an id add in no fixed order).
+// dW[id - v0] += dY[row] over the gathered rows whose id is in range, in fp32.
+// One atomic row per token was bound by the atomics: a few ids repeat often in
+// text, so their rows were added one after another at the same addresses, and
+// a lane's 8 consecutive columns spread every atomic instruction over 16 cache
+// lines.  Now chunks of kEmbChunk tokens are sorted by id (embed_sort, in the
+// stashed ids, which the backward consumes), a workgroup walks a window of
+// kEmbWin sorted tokens over 1024 columns and adds each run of equal ids up in
+// registers before one atomic add per column, consecutive lanes on consecutive
+// columns.  8192 tokens of hidden 4096 over a shard of 32064 (heavy-tailed ids,
+// a quarter of them in the shard): 627 -> 15 (sort) + 28 us.
+constexpr int kEmbChunk = 2048, kEmbWin = 16;
+
+// Keys (id - v0) << 32 | token, out-of-range ids as all ones, sorted ascending
+// per chunk in place: a bitonic network over LDS (66 steps, one exchange per
+// thread and step).
+__global__ void __launch_bounds__(kEmbChunk / 2) embed_sort_kernel(uint64_t* keys, int64_t v0, int32_t v_t, int64_t n) {
+  __shared__ uint64_t k[kEmbChunk];
+  const int tid = threadIdx.x;
+  const int64_t base = static_cast<int64_t>(blockIdx.x) * kEmbChunk;
+#pragma unroll
+  for (int i = tid; i < kEmbChunk; i += kEmbChunk / 2) {
+    uint64_t key = ~0ull;
+    if (base + i < n) {
+      const int64_t j = static_cast<int64_t>(keys[base + i]) - v0;
+      if (j >= 0 && j < v_t) key = static_cast<uint64_t>(j) << 32 | static_cast<uint32_t>(base + i);
+    }
+    k[i] = key;
+  }
+  for (int len = 2; len <= kEmbChunk; len <<= 1)
+    for (int half = len >> 1; half > 0; half >>= 1) {
+      __syncthreads();
+      const int i = 2 * tid - (tid & (half - 1)), j = i + half;   // pairs (i, i + half)
+      const uint64_t a = k[i], b = k[j];
+      if ((a > b) == ((i & len) == 0)) {
+        k[i] = b;
+        k[j] = a;
+      }
+    }
+  __syncthreads();
+#pragma unroll
+  for (int i = tid; i < kEmbChunk; i += kEmbChunk / 2)
+    if (base + i < n) keys[base + i] = k[i];
+}
+
+// SORTED: ids holds embed_sort's keys, else the raw ids in token order.
+template <bool SORTED>
 __global__ void __launch_bounds__(256) embed_bwd_kernel(const int64_t* __restrict__ ids, RowSrc dy, int64_t v0,
                                                        int32_t v_t, int32_t h, int64_t rows, float* __restrict__ dw) {
-  const int lane = threadIdx.x & 63;
-  const int64_t m = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (m >= rows) return;
-  const int64_t j = ids[m] - v0;
-  if (j < 0 || j >= v_t) return;
-  const u32x4* src = reinterpret_cast<const u32x4*>(dy.row(m));
-  float* d = dw + j * h;
-  for (int c = lane; c < h / 8; c += 64) {
-    float f[8];
-    unpack8(src[c], f);
+  const int64_t p0 = static_cast<int64_t>(blockIdx.x) * kEmbWin;
+  const int nw = static_cast<int>(rows - p0 < kEmbWin ? rows - p0 : kEmbWin);
+  const int col = blockIdx.y * 1024 + threadIdx.x;
+  // the window's ids and rows, wave-uniform values
+  int64_t cur = -1;
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  const auto flush = [&] {
+    if (cur < 0) return;
+    float* d = dw + cur * h;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) unsafeAtomicAdd(d + c * 8 + e, f[e]);
+    for (int q = 0; q < 4; ++q)
+      if (col + 256 * q < h) unsafeAtomicAdd(d + col + 256 * q, acc[q]);
+  };
+  for (int w0 = 0; w0 < nw; w0 += 4) {
+    int64_t id[4];
+    uint16_t v[4][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {       // four rows' loads in flight
+      id[u] = -1;
+      if (w0 + u < nw) {
+        int64_t m = p0 + w0 + u, j;
+        if constexpr (SORTED) {
+          const uint64_t key = static_cast<uint64_t>(ids[m]);
+          j = key == ~0ull ? -1 : static_cast<int64_t>(key >> 32);
+          m = static_cast<uint32_t>(key);
+        } else {
+          j = ids[m] - v0;
+        }
+        if (j >= 0 && j < v_t) {
+          id[u] = j;
+          const uint16_t* src = dy.row(m);
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (col + 256 * q < h) v[u][q] = src[col + 256 * q];
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (id[u] < 0) continue;
+      if (id[u] != cur) {
+        flush();
+        cur = id[u];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] = 0.f;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (col + 256 * q < h) acc[q] += __uint_as_float(static_cast<uint32_t>(v[u][q]) << 16);
+    }
   }
+  flush();
 }
 
 }  // namespace
@@ -694,18 +779,25 @@ hipError_t xent_grad(const float* probs, int64_t n, int32_t v_t, int64_t v0, con
 
 hipError_t embed_fwd(const int64_t* ids, const uint16_t* w, int64_t v0, int32_t v_t, int32_t h, int64_t rows,
                      int32_t s_c, int32_t s_sp, int32_t r, int32_t t, const uint16_t* receipt, uint16_t* own,
-                     uint16_t* send, hipStream_t stream) {
+                     uint16_t* send, int64_t* kept, hipStream_t stream) {
   if (rows <= 0) return hipSuccess;
   hipLaunchKernelGGL(embed_fwd_kernel, dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0, stream, ids, w,
-                     v0, v_t, h, rows, SpRows{s_c, s_sp, r, t}, receipt, own, send);
+                     v0, v_t, h, rows, SpRows{s_c, s_sp, r, t}, receipt, own, send, kept);
   return hipGetLastError();
 }
 
-hipError_t embed_bwd(const int64_t* ids, RowSrc dy, int64_t v0, int32_t v_t, int32_t h, int64_t rows, float* dw,
+hipError_t embed_bwd(int64_t* ids, RowSrc dy, int64_t v0, int32_t v_t, int32_t h, int64_t rows, float* dw,
                      hipStream_t stream) {
   if (rows <= 0) return hipSuccess;
-  hipLaunchKernelGGL(embed_bwd_kernel, dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0, stream, ids, dy,
-                     v0, v_t, h, rows, dw);
+  const dim3 grid(static_cast<unsigned>((rows + kEmbWin - 1) / kEmbWin), static_cast<unsigned>((h + 1023) / 1024));
+  // few tokens share few ids, and the sort would cost a launch of its own
+  if (rows <= 512) {
+    hipLaunchKernelGGL(embed_bwd_kernel<false>, grid, dim3(256), 0, stream, ids, dy, v0, v_t, h, rows, dw);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(embed_sort_kernel, dim3(static_cast<unsigned>((rows + kEmbChunk - 1) / kEmbChunk)),
+                     dim3(kEmbChunk / 2), 0, stream, reinterpret_cast<uint64_t*>(ids), v0, v_t, rows);
+  hipLaunchKernelGGL(embed_bwd_kernel<true>, grid, dim3(256), 0, stream, ids, dy, v0, v_t, h, rows, dw);
   return hipGetLastError();
 }
 

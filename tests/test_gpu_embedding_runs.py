@@ -1,0 +1,49 @@
+"""GPU parity of the embedding gradient where its sorted runs can go wrong:
+token counts around a sort chunk (2048) and the unsorted limit (512), hidden
+sizes that are no multiple of a column block (1024), one id on every token, no
+id in range, against a float64 sum.  fp32 sums of at most n terms of either
+sign: within n * 2^-24 of the sum of magnitudes."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2411_06465_amd as L
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,h,ids", [(8, 256, "mixed"), (512, 256, "mixed"), (520, 1280, "mixed"), (2048, 256, "same"),
+                                     (2056, 256, "mixed"), (4104, 768, "same"), (2056, 256, "none")])
+def test_gradient_matches_float64(n, h, ids):
+    print(f"\n[embedding runs n={n} h={h} {ids}]", flush=True)
+    v, t, rank = 4000, 4, 1
+    v_t = v // t
+    rng = np.random.default_rng(n + h)
+    if ids == "same":
+        tok = np.full(n, rank * v_t + 7)
+    elif ids == "none":
+        tok = rng.integers(0, v_t, n)
+    else:
+        tok = np.where(rng.random(n) < 0.3, rank * v_t + v_t - 1, rng.integers(0, v, n))
+    model, par = L.make_model(h, h // 64, h // 64, 32, vocab=v), L.make_parallel(n, tp=t, tp_rank=rank)
+    own, peer = n // t, n - n // t
+    dx = torch.randn(1, own, h, device="cuda").to(torch.bfloat16)
+    pdx = torch.randn(1, peer, h, device="cuda").to(torch.bfloat16)
+    table = torch.randn(v_t, h, device="cuda").to(torch.bfloat16)
+    buf = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    arena = L.Arena.on(buf)
+    ids_t = torch.from_numpy(tok.astype(np.int64)).cuda().view(1, n)
+    x = torch.empty(1, own, h, dtype=torch.bfloat16, device="cuda")
+    send = torch.empty(1, peer, h, dtype=torch.bfloat16, device="cuda")
+    st = L.embedding_fwd(model, par, ids_t, table, x, arena, send=send)
+    dw = torch.ones(v_t, h, device="cuda")
+    L.embedding_bwd(model, par, st, dx, dw, arena, peer_dx=pdx)
+    torch.cuda.synchronize()
+    assert arena.stats()["in_use"] == 0
+    assert torch.equal(ids_t.cpu().view(-1), torch.from_numpy(tok.astype(np.int64)))   # the caller's ids stay
+    full = torch.cat([pdx[:, :rank * own], dx, pdx[:, rank * own:]], 1)[0].double()
+    local = ids_t.view(-1) - rank * v_t
+    hit = (local >= 0) & (local < v_t)
+    ref = torch.ones(v_t, h, device="cuda", dtype=torch.float64).index_add_(0, local[hit], full[hit])
+    mag = torch.ones(v_t, h, device="cuda", dtype=torch.float64).index_add_(0, local[hit], full[hit].abs())
+    assert bool(((dw.double() - ref).abs() <= n * 2.0 ** -24 * mag).all())
