@@ -50,9 +50,11 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr int KT = 64;            // keys per tile (forward, dQ)
-constexpr int QT = 64;            // queries per tile (dK/dV)
+constexpr int QT = 32;            // queries per tile (dK/dV)
+constexpr float kMaxLag = 8.f;    // forward: growth of a row's maximum before a rescale, in base-2 exponents
+constexpr int kDkvStages = 4;     // dK/dV: query tiles in the copy ring (even: the handover buffer is the stage's parity)
 // LDS fragment reads kept in flight ahead of the products, per kernel
-constexpr int kLookFwd = 6, kLookDq = 4, kLookDkv = 4;
+constexpr int kLookFwd = 6, kLookDq = 4;
 
 __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 // Two floats to a packed bf16 pair with one conversion (round to nearest even).
@@ -112,15 +114,16 @@ __device__ __forceinline__ int swz(int row) {
 // wait for their own copies (vmcnt) before the barrier that publishes a tile.
 // The LDS address is uniform by construction; readfirstlane states it for the
 // compiler, which otherwise may keep it in a vector register.
-__device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, const uint8_t* lds) {
-  const uint32_t l = __builtin_amdgcn_readfirstlane(
-      static_cast<uint32_t>(reinterpret_cast<uintptr_t>(LPTR(const_cast<uint8_t*>(lds)))));
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(l) : "memory", "m0");
+__device__ __forceinline__ uint32_t lds_addr(const void* lds) {
+  return __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(LPTR(const_cast<void*>(lds)))));
 }
-__device__ __forceinline__ void dma4(const void* sbase, uint32_t voff, const void* lds) {
-  const uint32_t l = __builtin_amdgcn_readfirstlane(
-      static_cast<uint32_t>(reinterpret_cast<uintptr_t>(LPTR(const_cast<void*>(lds)))));
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" ::"v"(voff), "s"(sbase), "s"(l) : "memory", "m0");
+template <int IMM>
+__device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t lds) {   // LDS chunk at lds + IMM
+  asm volatile("s_add_u32 m0, %2, %3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds), "n"(IMM)
+               : "memory", "m0", "scc");
+}
+__device__ __forceinline__ void dma4(const void* sbase, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" ::"v"(voff), "s"(sbase), "s"(lds) : "memory", "m0");
 }
 
 // Copy rows [0, ROWS) of src (row stride ld, rows >= n_valid clamped to the
@@ -128,34 +131,45 @@ __device__ __forceinline__ void dma4(const void* sbase, uint32_t voff, const voi
 // A copy instruction moves RPK whole rows (1 KB); lane i lands at byte 16 i of
 // the instruction's LDS chunk.  The wave's copies start at rows that agree
 // modulo 4 * RPK (the waves take every NW-th chunk, NW a multiple of 4), which
-// fixes swz, so each lane's swizzled source column is fixed: the row block is
-// a uniform base and the lane adds one 32-bit byte offset, except on a ragged tail.
+// fixes swz, so each lane's swizzled source column is fixed: its byte offsets are
+// formed once, and a copy is two instructions on a uniform base, except on a
+// ragged tail.
 template <int D, int ROWS, int NW = 4>
-__device__ __forceinline__ void tile_load(uint8_t* lds, const uint16_t* src, int64_t ld, int n_valid, int wave,
-                                          int lane) {
-  constexpr int CH = D / 8;              // 16-byte chunks per row
-  constexpr int RPK = 64 / CH;           // rows per 1 KB wave chunk
-  constexpr int NKB = ROWS / RPK;
+struct TileCopy {
+  static constexpr int CH = D / 8;              // 16-byte chunks per row
+  static constexpr int RPK = 64 / CH;           // rows per 1 KB wave chunk
+  static constexpr int NKB = ROWS / RPK;
   static_assert(NKB % NW == 0, "every wave issues the same number of copies");
-  const int lrow = lane / CH;
-  const int lc = (lane % CH) ^ swz<D>(wave * RPK + lrow);   // the same for every copy of this wave
-  const int ldb = static_cast<int>(ld) * 2;                 // row stride in bytes
-  if (n_valid >= ROWS) {
-    const uint32_t lane_off = static_cast<uint32_t>(lrow * ldb + lc * 16);
+  int row0, lc, ldb;            // the lane's row in the first copy, its chunk, the row stride in bytes
+  uint32_t off[NKB / NW];       // byte offset of the lane's 16 bytes of each copy
+  uint32_t lds0;                // the wave's chunk within a tile
+  __device__ __forceinline__ TileCopy(int64_t ld, int wave, int lane) {
+    row0 = wave * RPK + lane / CH;
+    lc = (lane % CH) ^ swz<D>(row0);            // the same for every copy of this wave
+    ldb = static_cast<int>(ld) * 2;
 #pragma unroll
-    for (int j = 0; j < NKB / NW; ++j) {
-      const int q = wave + j * NW;
-      dma16(src + static_cast<int64_t>(q * RPK) * ld, lane_off, lds + q * 1024);
-    }
-  } else {                               // ragged tail: rows past n_valid repeat the last valid row
+    for (int j = 0; j < NKB / NW; ++j) off[j] = static_cast<uint32_t>((row0 + j * NW * RPK) * ldb + lc * 16);
+    lds0 = wave * 1024;
+  }
+  __device__ __forceinline__ void operator()(uint32_t lds, const uint16_t* src, int n_valid) const {
+    if (n_valid >= ROWS) {
+      each<0>(lds + lds0, src, off);
+    } else {                               // ragged tail: rows past n_valid repeat the last valid row
+      uint32_t o[NKB / NW];
 #pragma unroll
-    for (int j = 0; j < NKB / NW; ++j) {
-      const int q = wave + j * NW;
-      const int r = min(q * RPK + lrow, n_valid - 1);
-      dma16(src, static_cast<uint32_t>(r * ldb + lc * 16), lds + q * 1024);
+      for (int j = 0; j < NKB / NW; ++j)
+        o[j] = static_cast<uint32_t>(min(row0 + j * NW * RPK, n_valid - 1) * ldb + lc * 16);
+      each<0>(lds + lds0, src, o);
     }
   }
-}
+  template <int J>
+  __device__ __forceinline__ void each(uint32_t lds, const uint16_t* src, const uint32_t (&o)[NKB / NW]) const {
+    if constexpr (J < NKB / NW) {
+      dma16<J * NW * 1024>(src, o[J], lds);
+      each<J + 1>(lds, src, o);
+    }
+  }
+};
 
 // Per-lane LDS byte offsets of the two fragment shapes below, at kk = 0 and
 // dt = 0 of a tile's first row block.  With swz periodic in 16 rows, the
@@ -246,59 +260,54 @@ __device__ __forceinline__ bool find_tile(const AttnParams& p, int tile, int tsz
 // wave with the softmax of another.
 //
 // The output and the row sum are rescaled only on tiles where some row's
-// maximum grew (a wave-wide vote).  The reference maximum stays exact: a
-// stale one would leave the largest probability of a row off the bf16 grid
-// point 1 and, for sharply peaked rows, double the rounding error of ctx.
+// maximum grew past the reference by more than kMaxLag (a wave-wide vote): the
+// reference may lag, which leaves probabilities up to 2^kMaxLag.  That costs no
+// precision, because P enters the product as two bf16 parts (about 16 bits at any
+// magnitude) and everything else is fp32; with the exact maximum about half of
+// the tiles of an 8192-key row block rescaled, 64 products each after a drain of
+// the matrix pipe.
 
-// Next key tile to visit at or after (seg, t0): the first tile of a segment
-// whose first key a query at pos_max can see.  Positions grow within a
-// segment, so the rest of a segment is skipped once a tile starts past pos_max.
-__device__ __forceinline__ bool next_tile(const AttnParams& p, int pos_max, int& seg, int& t0) {
-  while (seg < p.n_seg) {
-    if (t0 < p.seg[seg].n && p.seg[seg].pos0 + t0 <= pos_max) return true;
-    ++seg;
-    t0 = 0;
+// The key tiles of `step` keys that a query at pos_max can see, over the
+// segments in order: the first tile of a segment whose first key is visible and
+// the ones after it.  Positions grow within a segment, so the rest of a segment
+// is skipped once a tile starts past pos_max.  A segment's fields are loaded
+// when the walk enters it: loading them for every tile put several scalar loads,
+// each waited for, in front of every tile's products.
+struct Tile {
+  int kpos0, kvalid;           // position of its first key; keys, 0 = no tile
+};
+struct KeyWalk {
+  const AttnParams& p;
+  const int pos_max, step, bi;
+  const int64_t col, stride;   // the kv head's column; bytes per step (every segment has the same row stride)
+  int seg = -1, left = 0;      // segment; its keys from the next tile on (0 = none, or none visible)
+  int pos = 0;                 // position of the next tile's first key
+  uint64_t ka = 0, va = 0;     // addresses of the first rows of the tile last returned, at the kv head's column
+  __device__ __forceinline__ KeyWalk(const AttnParams& p_, int pos_max_, int step_, int bi_, int64_t col_)
+      : p(p_), pos_max(pos_max_), step(step_), bi(bi_), col(col_), stride(step_ * p_.seg[0].ld * 2) {}
+  __device__ __forceinline__ const uint16_t* k() const { return reinterpret_cast<const uint16_t*>(ka); }
+  __device__ __forceinline__ const uint16_t* v() const { return reinterpret_cast<const uint16_t*>(va); }
+  __device__ __forceinline__ Tile next() {
+    ka += stride;
+    va += stride;
+    while (left <= 0 || pos > pos_max) {
+      if (++seg >= p.n_seg) {
+        left = 0;              // stays at the end
+        seg = p.n_seg;
+        return Tile{0, 0};
+      }
+      const KvSeg& s = p.seg[seg];
+      left = s.n;
+      pos = s.pos0;
+      ka = reinterpret_cast<uint64_t>(s.k + bi * s.bstride + col);
+      va = reinterpret_cast<uint64_t>(s.v + bi * s.bstride + col);
+    }
+    const Tile t{pos, min(step, left)};
+    pos += step;
+    left -= step;
+    return t;
   }
-  return false;
-}
-
-// Two-stage copy ring over the key tiles of `step` keys that a query at
-// pos_max can see: tile j is computed from buffer j % 2 while tile j + 1 lands
-// in the other.  `issue(seg, t0, buf)` starts a tile's copies, `compute(seg,
-// t0, buf)` uses it; buf is std::integral_constant<int, 0 or 1>, so every LDS
-// object is named statically and the compiler sees that reads of one buffer
-// do not depend on the copies landing in the other.
-template <class Issue, class Compute>
-__device__ __forceinline__ void run_ring2(const AttnParams& p, int pos_max, int step, Issue issue, Compute compute) {
-  using B0 = std::integral_constant<int, 0>;
-  using B1 = std::integral_constant<int, 1>;
-  int cs = 0, ct = 0;
-  bool have = next_tile(p, pos_max, cs, ct);
-  if (have) issue(cs, ct, B0{});
-  while (have) {
-    int ns = cs, nt = ct + step;
-    bool more = next_tile(p, pos_max, ns, nt);
-    wait_copies<0>();
-    ring_barrier();                      // every wave's copy is visible; the other buffer is free
-    if (more) issue(ns, nt, B1{});
-    __builtin_amdgcn_sched_barrier(0);   // the copies go out now, not next to the wait for them
-    compute(cs, ct, B0{});
-    if (!more) break;
-    cs = ns;
-    ct = nt;
-    ns = cs;
-    nt = ct + step;
-    more = next_tile(p, pos_max, ns, nt);
-    wait_copies<0>();
-    ring_barrier();
-    if (more) issue(ns, nt, B0{});
-    __builtin_amdgcn_sched_barrier(0);
-    compute(cs, ct, B1{});
-    have = more;
-    cs = ns;
-    ct = nt;
-  }
-}
+};
 
 // ------------------------------------------------------------------ pipelined products
 // Two accumulator chains over the D columns of LDS tiles, with the B operands
@@ -346,32 +355,11 @@ __device__ __forceinline__ void accum_t(const uint8_t* lds, const bf16x8 (&x)[NG
   __builtin_amdgcn_sched_group_barrier(0x008, L, 0);
 }
 
-// acc[dt] += A^T (xh + xl): as accum_t with the register operand split into a
-// high and a low bf16 part; each transposed fragment feeds both products, and
-// the high products of a group's column blocks go before their low products,
-// so no product waits on the one just before it.
-template <int D, int NG, int LA>
-__device__ __forceinline__ void accum_t2(const uint8_t* lds, const bf16x8 (&xh)[NG], const bf16x8 (&xl)[NG],
-                                         f32x16 (&acc)[D / 32], LaneAddr la) {
-  constexpr int N = NG * D / 32;
-  constexpr int L = LA < N ? LA : N - 1;
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    bf16x8 f[D / 32];
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) f[dt] = frag_cols<D>(lds, dt, g, la);
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) acc[dt] = mfma(f[dt], xh[g], acc[dt]);
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) acc[dt] = mfma(f[dt], xl[g], acc[dt]);
-  }
-  __builtin_amdgcn_sched_group_barrier(0x100, 2 * L, 0);
-#pragma unroll
-  for (int i = 0; i < N - L; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-  }
-  __builtin_amdgcn_sched_group_barrier(0x008, 2 * L, 0);
+// max(x, x of the other half-wave), in every lane
+__device__ __forceinline__ float half_max(float x) {
+  const u32x2 r = __builtin_bit_cast(
+      u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false));
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
 template <int D>
@@ -408,33 +396,36 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
   for (int i = 0; i < D / 32; ++i) o[i] = f32x16{};
 
-  auto issue = [&](int seg, int t0, uint8_t* kt, uint8_t* vt) __attribute__((always_inline)) {
-    const KvSeg& s = p.seg[seg];
-    const int64_t off = bi * s.bstride + static_cast<int64_t>(t0) * s.ld + hk * D;
-    tile_load<D, KT>(kt, s.k + off, s.ld, s.n - t0, wave, lane);
-    tile_load<D, KT>(vt, s.v + off, s.ld, s.n - t0, wave, lane);
+  KeyWalk walk(p, pos_max, KT, bi, hk * D);
+  const TileCopy<D, KT> copy(p.seg[0].ld, wave, lane);
+  const uint32_t ka0 = lds_addr(k0), ka1 = lds_addr(k1), va0 = lds_addr(v0), va1 = lds_addr(v1);
+  // maximum of a lane's 32 scores: a chain of three-input maxima
+  const auto row_max = [](const f32x16 (&s)[2]) __attribute__((always_inline)) {
+    float m = __builtin_fmaxf(s[0][0], s[0][1]);
+#pragma unroll
+    for (int i = 2; i < 16; i += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, s[0][i]), s[0][i + 1]);
+#pragma unroll
+    for (int i = 0; i < 16; i += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, s[1][i]), s[1][i + 1]);
+    return m;
   };
-  auto compute = [&](int seg, int t0, const uint8_t* kt, const uint8_t* vt) __attribute__((always_inline)) {
-    const int kpos0 = p.seg[seg].pos0 + t0;
-    const int kvalid = min(KT, p.seg[seg].n - t0);
-    f32x16 sc[2] = {f32x16{}, f32x16{}};
-    scores2<D, kLookFwd>(kt, 0, qf, sc[0], kt, 32, qf, sc[1], la);
-    if (kpos0 + KT - 1 > pos_min || kvalid < KT) {       // tile straddles the diagonal (or is ragged)
+  // One key tile, its scores already in s (their maximum in mx): the softmax and
+  // O += V^T P, with the next tile's scores S^T = K Q^T (into sn, mxn) computed
+  // under the exponentials.  After the last tile sn comes from stale LDS and is
+  // never used.
+  const auto step = [&](Tile t, const uint8_t* vt, const uint8_t* kt_next, f32x16 (&s)[2], float mx, f32x16 (&sn)[2],
+                        float& mxn) __attribute__((always_inline)) {
+    if (t.kpos0 + KT - 1 > pos_min || t.kvalid < KT) {     // tile straddles the diagonal (or is ragged)
       // last visible key row for this query, relative to the lane's first row
-      const int lim = min(my_pos - kpos0, kvalid - 1) - rbase;
+      const int lim = min(my_pos - t.kpos0, t.kvalid - 1) - rbase;
 #pragma unroll
       for (int t2 = 0; t2 < 2; ++t2)
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-          if (t2 * 32 + 8 * (i >> 2) + (i & 3) > lim) sc[t2][i] = -INFINITY;
+          if (t2 * 32 + 8 * (i >> 2) + (i & 3) > lim) s[t2][i] = -INFINITY;
+      mx = row_max(s);
     }
-    float mx = __builtin_fmaxf(sc[0][0], sc[0][1]);           // a chain of three-input maxima
-#pragma unroll
-    for (int i = 2; i < 16; i += 2) mx = __builtin_fmaxf(__builtin_fmaxf(mx, sc[0][i]), sc[0][i + 1]);
-#pragma unroll
-    for (int i = 0; i < 16; i += 2) mx = __builtin_fmaxf(__builtin_fmaxf(mx, sc[1][i]), sc[1][i + 1]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c;
-    if (__builtin_amdgcn_ballot_w64(mx > m_run)) {
+    mx = half_max(mx) * c;
+    if (__builtin_amdgcn_ballot_w64(mx > m_run + kMaxLag)) {
       const float m_new = fmaxf(m_run, mx);
       const float alpha = m_new == -INFINITY ? 1.f : fast_exp2(m_run - m_new);   // 0 while m_run is -inf
 #pragma unroll
@@ -443,38 +434,101 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
       m_run = m_new;
     }
     const float m_use = m_run == -INFINITY ? 0.f : m_run;
-    float rs = 0.f;
+    sn[0] = f32x16{};
+    sn[1] = f32x16{};
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk) {
+      sn[0] = mfma(frag_rows<D>(kt_next, 0, kk, la), qf[kk], sn[0]);
+      sn[1] = mfma(frag_rows<D>(kt_next, 32, kk, la), qf[kk], sn[1]);
+    }
+    float rs[2] = {0.f, 0.f};
 #pragma unroll
     for (int t2 = 0; t2 < 2; ++t2)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const float pr = fast_exp2(fmaf(sc[t2][i], c, -m_use));
-        sc[t2][i] = pr;
-        rs += pr;
+        const float pr = fast_exp2(fmaf(s[t2][i], c, -m_use));
+        s[t2][i] = pr;
+        rs[i & 1] += pr;
       }
-    l_run += rs;
+    l_run += rs[0] + rs[1];
     // P enters the P V product as bf16 hi + lo parts (two products per V
     // fragment): a plain bf16 P carries a relative error of up to 2^-9 into
-    // every output, which the bf16 stores after attention then amplify.
-    bf16x8 pf[4], pl[4];
+    // every output, which the bf16 stores after attention then amplify.  The
+    // high products of a group's column blocks go before their low products,
+    // so no product waits on the one just before it; the next group's split and
+    // V fragments go between them.
+    bf16x8 ph[2], pl[2], f[2][D / 32];
+    const auto group = [&](int g) __attribute__((always_inline)) {
+      ph[g & 1] = frag_acc(s[g >> 1], 8 * (g & 1));
+      pl[g & 1] = frag_acc_lo(s[g >> 1], 8 * (g & 1), ph[g & 1]);
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt) f[g & 1][dt] = frag_cols<D>(vt, dt, g, la);
+    };
+    group(0);
+    // the score products: an LDS read (kLookFwd ahead), exponentials and their sums between every two
+    constexpr int NS = D / 8, NV = 2 * (D / 32);
+    __builtin_amdgcn_sched_group_barrier(0x100, kLookFwd, 0);
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);            // MFMA
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);            // LDS read
+      __builtin_amdgcn_sched_group_barrier(0x400, 32 / NS, 0);      // exponentials
+      __builtin_amdgcn_sched_group_barrier(0x002, 96 / NS, 0);      // other VALU
+    }
+    __builtin_amdgcn_sched_group_barrier(0x100, NV, 0);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      pf[g] = frag_acc(sc[g >> 1], 8 * (g & 1));
-      pl[g] = frag_acc_lo(sc[g >> 1], 8 * (g & 1), pf[g]);
+      if (g < 3) group(g + 1);
+      else mxn = row_max(sn);
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt) o[dt] = mfma(f[g & 1][dt], ph[g & 1], o[dt]);
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt) o[dt] = mfma(f[g & 1][dt], pl[g & 1], o[dt]);
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 24 / NV, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
-    accum_t2<D, 4, kLookFwd>(vt, pf, pl, o, la);
   };
 
-  run_ring2(
-      p, pos_max, KT,
-      [&](int seg, int t0, auto b) __attribute__((always_inline)) {
-        if constexpr (decltype(b)::value == 0) issue(seg, t0, k0, v0);
-        else issue(seg, t0, k1, v1);
-      },
-      [&](int seg, int t0, auto b) __attribute__((always_inline)) {
-        if constexpr (decltype(b)::value == 0) compute(seg, t0, k0, v0);
-        else compute(seg, t0, k1, v1);
-      });
+  // Two buffers each for K and V.  While tile j is in step, V_j and K_(j+1) are
+  // in use, V_(j+1) and K_(j+2) land in the buffers that V_(j-1) and K_j held.
+  Tile t = walk.next();
+  if (t.kvalid) {
+    copy(ka0, walk.k(), t.kvalid);
+    copy(va0, walk.v(), t.kvalid);
+    Tile t1 = walk.next();
+    const uint16_t* v_next = walk.v();       // V of tile t1
+    if (t1.kvalid) copy(ka1, walk.k(), t1.kvalid);
+    wait_copies<0>();
+    ring_barrier();
+    f32x16 sa[2] = {f32x16{}, f32x16{}}, sb[2];
+    scores2<D, kLookFwd>(k0, 0, qf, sa[0], k0, 32, qf, sa[1], la);
+    float ma = row_max(sa), mb = -INFINITY;
+    const auto turn = [&](const uint8_t* vt, uint32_t va_next, uint32_t ka, const uint8_t* kt_next, f32x16 (&s)[2],
+                          float mx, f32x16 (&sn)[2], float& mxn) __attribute__((always_inline)) {
+      const Tile t2 = walk.next();
+      wait_copies<0>();
+      ring_barrier();                      // every wave's copies are visible and the two old buffers are free
+      if (t1.kvalid) copy(va_next, v_next, t1.kvalid);
+      if (t2.kvalid) copy(ka, walk.k(), t2.kvalid);
+      __builtin_amdgcn_sched_barrier(0);   // the copies go out now, not next to the wait for them
+      step(t, vt, kt_next, s, mx, sn, mxn);
+      t = t1;
+      t1 = t2;
+      v_next = walk.v();
+    };
+    while (true) {
+      turn(v0, va1, ka0, k1, sa, ma, sb, mb);
+      if (!t.kvalid) break;
+      turn(v1, va0, ka1, k0, sb, mb, sa, ma);
+      if (!t.kvalid) break;
+    }
+  }
 
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   if (!q_ok) return;
@@ -517,12 +571,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 template <int D>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) attn_bwd_dkdv_kernel(AttnParams p) {
   constexpr int TB = QT * D * 2;
-  // Two stages of Q and dO tiles (64 KB at D = 128: every tile offset fits a
-  // ds_read immediate), then the statistics and the P^T handover.
-  __shared__ __attribute__((aligned(16))) uint8_t qg0[2][TB], qg1[2][TB];   // per stage: Q tile, then dO tile
-  __shared__ __attribute__((aligned(16))) float st0[2][QT], st1[2][QT];             // lse, delta
-  // P^T handover in fp32, so that dS^T = P^T (dP^T - delta) rounds once: [group][16 queries][half][lane]
-  __shared__ __attribute__((aligned(16))) float4 xp[4][QT / 16][2][64];
+  // Four stages of Q and dO tiles (64 KB at D = 128: every tile offset fits a
+  // ds_read immediate), their statistics, and two P^T handovers.
+  __shared__ __attribute__((aligned(16))) uint8_t qg[kDkvStages][2][TB];   // per stage: Q tile, then dO tile
+  __shared__ __attribute__((aligned(16))) float st[kDkvStages][2][QT];    // lse, delta
+  // P^T handover in fp32, so that dS^T = P^T (dP^T - delta) rounds once: [buffer][group][16 queries][half][lane]
+  __shared__ __attribute__((aligned(16))) float4 xp[2][4][QT / 16][2][64];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = wave & 3, role = wave >> 2;
@@ -563,129 +617,182 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   for (int i = 0; i < D / 32; ++i) acc[i] = f32x16{};
   const float c = p.scale * kLog2e;
   const int n_qt = (p.n_q + QT - 1) / QT;
-  const int total = hpb * n_qt;
   const int head0 = hk * group + split * hpb;
-  auto next_wanted = [&](int from) __attribute__((always_inline)) {
-    for (int it = from; it < total; ++it) {
-      const int qt = it % n_qt;
-      const int last = min(qt * QT + QT - 1, p.n_q - 1);
-      if (qpos(p.qmap, last) >= blk_kpos0) return it;
-    }
-    return total;
+  // The query tiles that see the block: local rows are in position order, so
+  // those from qt0 on, of each of the hpb heads.
+  int qt0 = 0;
+  while (qt0 < n_qt && qpos(p.qmap, min(qt0 * QT + QT - 1, p.n_q - 1)) < blk_kpos0) ++qt0;
+  const int per_head = n_qt - qt0;
+  // waves 0-3 copy the Q tiles and their lse, waves 4-7 the dO tiles and delta
+  const TileCopy<D, QT> copy(p.q_ld, grp, lane);
+  const uint32_t qg_addr = lds_addr(qg) + role * TB, st_addr = lds_addr(st) + (role * QT + grp * (QT / 4)) * 4;
+  // the next tile to copy: its first row, its head's statistics, its query tile, tiles left to copy after it
+  // (the role's pointers by arithmetic: a select of the two members' addresses
+  // would put the kernel argument on the stack)
+  const auto pick = [&](const void* a, const void* b) {
+    const uint64_t x = reinterpret_cast<uint64_t>(a), y = reinterpret_cast<uint64_t>(b);
+    return x + ((y - x) & (0ull - static_cast<uint64_t>(role)));
   };
-  auto issue = [&](int it, uint8_t* qt_l, uint8_t* gt_l, float (*st)[QT]) __attribute__((always_inline)) {
-    const int hq = head0 + it / n_qt, qt = it % n_qt;
-    if (lane < 16) {    // waves 0-3 copy the lse, waves 4-7 delta, of queries 16 grp .. 16 grp + 15
-      const int q = min(qt * QT + grp * 16 + lane, p.n_q - 1);
-      const float* row = (role == 0 ? p.lse : p.delta) + (static_cast<int64_t>(bi) * p.a_t + hq) * p.n_q;
-      dma4(row, static_cast<uint32_t>(q) * 4u, &st[role][grp * 16]);
-    }
-    const int64_t off = bi * p.q_bstride + static_cast<int64_t>(qt * QT) * p.q_ld + hq * D;
-    tile_load<D, QT, 8>(qt_l, p.q + off, p.q_ld, p.n_q - qt * QT, wave, lane);
-    tile_load<D, QT, 8>(gt_l, p.dout + off, p.q_ld, p.n_q - qt * QT, wave, lane);
+  uint64_t src = pick(p.q, p.dout) + (bi * p.q_bstride + static_cast<int64_t>(qt0) * QT * p.q_ld + head0 * D) * 2;
+  uint64_t row = pick(p.lse, p.delta) + (static_cast<int64_t>(bi) * p.a_t + head0) * p.n_q * 4;
+  const int64_t tile_step = static_cast<int64_t>(QT) * p.q_ld * 2, head_step = D * 2 - (per_head - 1) * tile_step;
+  int copy_qt = qt0, copy_left = hpb * per_head - 1;
+  // Copies that tile into stage b, kCopies per wave, and moves on; past the last
+  // tile it repeats it, so that the waits count exactly.
+  constexpr int kCopies = TileCopy<D, QT>::NKB / 4 + 1;
+  auto issue = [&](int b) __attribute__((always_inline)) {
+    const int q0 = copy_qt * QT;
+    if (lane < QT / 4)
+      dma4(reinterpret_cast<const float*>(row), static_cast<uint32_t>(min(q0 + grp * (QT / 4) + lane, p.n_q - 1)) * 4u,
+           st_addr + b * (2 * QT * 4));
+    copy(qg_addr + b * (2 * TB), reinterpret_cast<const uint16_t*>(src), p.n_q - q0);
+    const bool more = copy_left > 0, wrap = copy_qt + 1 == n_qt;
+    src += more ? (wrap ? head_step : tile_step) : 0;
+    row += more && wrap ? static_cast<int64_t>(p.n_q) * 4 : 0;
+    copy_qt = more ? (wrap ? qt0 : copy_qt + 1) : copy_qt;
+    copy_left -= more;
   };
-  // One query tile (64 queries as four 16-query groups g; MFMA halves h = g / 2).
-  auto compute = [&](int it, const uint8_t* qt_l, const uint8_t* gt_l, const float (*st)[QT]) __attribute__((always_inline)) {
-    const int qt = it % n_qt;
+  f32x16 s;                  // role 0: S^T -> P^T of a tile, role 1: its dP^T
+  bf16x8 x[2];               // role 0: P^T, role 1: dS^T (bf16)
+  // role 0: P^T = exp(S^T - lse) of tile qt from its scores in s; bf16 into x, fp32 into handover hb
+  auto probs = [&](int qt, const float4 (&ls4)[4], float4 (*hb)[2][64]) __attribute__((always_inline)) {
     const int qr0 = qt * QT;
     const int qlast = min(qr0 + QT - 1, p.n_q - 1);
     const int qp0 = qpos(p.qmap, qr0), qpl = qpos(p.qmap, qlast);
-    // Every group works on every tile the block visits; on the one or two
-    // diagonal tiles where all of a group's keys follow every query, the
-    // causal mask zeroes its P^T (a skip there would cost register copies at
-    // the branch joins on every tile).
-    const bool full = qp0 >= grp_kpos0 + 31 && qlast == qr0 + QT - 1 && qpl - qp0 == QT - 1;
-    const bool contiguous = qpl - qp0 == qlast - qr0;
-    // Both roles run one instruction stream over role-selected tiles (role 0:
-    // S^T from Q, dV^T from dO; role 1: dP^T from dO, dK^T from Q), so the
-    // accumulators never meet at a branch join.
-    f32x16 s[2] = {f32x16{}, f32x16{}};              // role 0: S^T -> P^T, role 1: dP^T -> dS^T
-    bf16x8 x[4];                                       // role 0: P^T, role 1: dS^T (bf16)
-    scores2<D, kLookDkv>(qt_l, 0, kv, s[0], qt_l, 32, kv, s[1], la1);
-    {
-      if (role == 0) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+    for (int jj = 0; jj < 4; ++jj) {
+      const float4 ls = ls4[jj];
+      const float lsv[4] = {ls.x * kLog2e, ls.y * kLog2e, ls.z * kLog2e, ls.w * kLog2e};
 #pragma unroll
-          for (int jj = 0; jj < 4; ++jj) {
-            const float4 ls = *reinterpret_cast<const float4*>(&st[0][32 * h + 8 * jj + rbase]);
-            const float lsv[4] = {ls.x * kLog2e, ls.y * kLog2e, ls.z * kLog2e, ls.w * kLog2e};
+      for (int u = 0; u < 4; ++u) s[4 * jj + u] = fast_exp2(fmaf(s[4 * jj + u], c, -lsv[u]));
+    }
+    // Every group works on every tile the block visits; on the few diagonal
+    // tiles where all of a group's keys follow every query, the causal mask
+    // zeroes its P^T.
+    if (!(qp0 >= grp_kpos0 + 31 && qlast == qr0 + QT - 1 && qpl - qp0 == QT - 1)) {   // causal / ragged masks
+      if (qpl - qp0 == qlast - qr0) {
+        // visible query rows r (relative to the lane's first row): lo <= r <= hi
+        const int lo = (key_ok ? my_kpos - qp0 : QT) - rbase;
+        const int hi = qlast - qr0 - rbase;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) s[h][4 * jj + u] = fast_exp2(fmaf(s[h][4 * jj + u], c, -lsv[u]));
-          }
-        if (!full) {                                   // causal / ragged masks
-          if (contiguous) {
-            // visible query rows r (relative to the lane's first row): lo <= r <= hi
-            const int lo = (key_ok ? my_kpos - qp0 : QT) - rbase;
-            const int hi = qlast - qr0 - rbase;
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-              for (int i = 0; i < 16; ++i) {
-                const int r = 32 * h + 8 * (i >> 2) + (i & 3);
-                if (r < lo || r > hi) s[h][i] = 0.f;
-              }
-          } else {                                     // the tile spans two context-parallel chunks
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-              for (int i = 0; i < 16; ++i) {
-                const int qr = 32 * h + 8 * (i >> 2) + rbase + (i & 3);
-                const int qp = qr0 + qr <= qlast ? qpos(p.qmap, qr0 + qr) : -1;
-                if (my_kpos > qp || !key_ok) s[h][i] = 0.f;
-              }
-          }
+        for (int i = 0; i < 16; ++i) {
+          const int r = 8 * (i >> 2) + (i & 3);
+          if (r < lo || r > hi) s[i] = 0.f;
         }
+      } else {                                     // the tile spans two context-parallel chunks
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int h = g >> 1, i0 = 8 * (g & 1);
-          x[g] = frag_acc(s[h], i0);                   // bf16 P^T for this wave's dV product
-          xp[grp][g][0][lane] = make_float4(s[h][i0], s[h][i0 + 1], s[h][i0 + 2], s[h][i0 + 3]);
-          xp[grp][g][1][lane] = make_float4(s[h][i0 + 4], s[h][i0 + 5], s[h][i0 + 6], s[h][i0 + 7]);
+        for (int i = 0; i < 16; ++i) {
+          const int qr = 8 * (i >> 2) + rbase + (i & 3);
+          const int qp = qr0 + qr <= qlast ? qpos(p.qmap, qr0 + qr) : -1;
+          if (my_kpos > qp || !key_ok) s[i] = 0.f;
         }
       }
     }
-    ring_barrier();                                    // P^T of every group is visible to its partner
-    if (role == 1) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const float4 p0 = xp[grp][g][0][lane], p1 = xp[grp][g][1][lane];
-        const float pv[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
-        const int h = g >> 1, i0 = 8 * (g & 1);
-        const float4 d0 = *reinterpret_cast<const float4*>(&st[1][32 * h + (i0 >> 2) * 8 + rbase]);
-        const float4 d1 = *reinterpret_cast<const float4*>(&st[1][32 * h + ((i0 >> 2) + 1) * 8 + rbase]);
-        const float dev[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-        float ds[8];
+    for (int g = 0; g < 2; ++g) {
+      const int i0 = 8 * g;
+      x[g] = frag_acc(s, i0);
+      hb[g][0][lane] = make_float4(s[i0], s[i0 + 1], s[i0 + 2], s[i0 + 3]);
+      hb[g][1][lane] = make_float4(s[i0 + 4], s[i0 + 5], s[i0 + 6], s[i0 + 7]);
+    }
+  };
+  // role 1: dS^T = P^T (dP^T - delta) of the tile whose dP^T - delta is in s, into x
+  auto grads = [&](const float4 (*hb)[2][64]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) ds[j] = pv[j] * (s[h][i0 + j] - dev[j]);
-        x[g] = __builtin_bit_cast(
-            bf16x8, u32x4{pack2(ds[0], ds[1]), pack2(ds[2], ds[3]), pack2(ds[4], ds[5]), pack2(ds[6], ds[7])});
+    for (int g = 0; g < 2; ++g) {
+      const float4 p0 = hb[g][0][lane], p1 = hb[g][1][lane];
+      const float pv[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
+      float ds[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) ds[j] = pv[j] * s[8 * g + j];
+      x[g] = __builtin_bit_cast(
+          bf16x8, u32x4{pack2(ds[0], ds[1]), pack2(ds[2], ds[3]), pack2(ds[4], ds[5]), pack2(ds[6], ds[7])});
+    }
+  };
+  auto minus = [&](const float4 (&d4)[4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      s[4 * jj] -= d4[jj].x;
+      s[4 * jj + 1] -= d4[jj].y;
+      s[4 * jj + 2] -= d4[jj].z;
+      s[4 * jj + 3] -= d4[jj].w;
+    }
+  };
+  // Both roles run one stream of products over role-selected tiles (role 0: S^T
+  // from Q, dV^T from dO; role 1: dP^T from dO, dK^T from Q), so the accumulators
+  // never meet at a branch join: the next tile's scores (stage bn) alternating
+  // with this tile's accumulation (stage b) of x.
+  auto products = [&](int b, int bn, bool accumulate) __attribute__((always_inline)) {
+    s = f32x16{};
+    const uint8_t* tb = qg[b][0];
+    const uint8_t* tn = qg[bn][0];
+    constexpr int NS = D / 16, NA = 2 * (D / 32);     // products of either kind (equal)
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      s = mfma(frag_rows<D>(tn, 0, i, la1), kv[i], s);
+      if (accumulate) {
+        const int g = i / (D / 32), dt = i % (D / 32);
+        acc[dt] = mfma(frag_cols<D>(tb, dt, g, la2), x[g], acc[dt]);
       }
     }
-    __builtin_amdgcn_sched_barrier(0);
-    accum_t<D, 4, kLookDkv>(qt_l, x, acc, la2);
+    static_assert(NS == NA, "scores and accumulation alternate");
   };
 
-  // Two-stage ring over the query tiles: tile j is used from one buffer set
-  // while tile j + 1 lands in the other.
-  int cur = next_wanted(0);
-  if (cur < total) issue(cur, qg0[0], qg0[1], st0);
-  while (cur < total) {
-    int nxt = next_wanted(cur + 1);
-    wait_copies<0>();
-    ring_barrier();                      // tile cur is visible; the other buffers are free
-    if (nxt < total) issue(nxt, qg1[0], qg1[1], st1);
-    __builtin_amdgcn_sched_barrier(0);   // the copies go out now, not next to the wait for them
-    compute(cur, qg0[0], qg0[1], st0);
-    if (nxt >= total) break;
-    cur = nxt;
-    nxt = next_wanted(cur + 1);
-    wait_copies<0>();
+  // One barrier per tile.  Interval j, after the barrier that publishes tile
+  // j + 1 and the handover of P_j: role 1 forms dS_j; both roles run tile j's
+  // accumulation and tile j + 1's scores; role 0 forms and hands over P_(j+1).
+  // The two waves of a SIMD so have their VALU work at opposite ends of the
+  // interval, under the other's products.  The copies of tile j + 3 go out
+  // behind the products; past the last tile its scores are computed once more,
+  // unused.
+  if (qt0 < n_qt) {
+    float4 stat[4];            // the lane's rows of the next tile's lse (role 0) or delta (role 1)
+    const auto read_stat = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) stat[jj] = *reinterpret_cast<const float4*>(&st[b][role][8 * jj + rbase]);
+    };
+#pragma unroll
+    for (int b = 0; b < kDkvStages - 1; ++b) issue(b);
+    wait_copies<(kDkvStages - 2) * kCopies>();
     ring_barrier();
-    if (nxt < total) issue(nxt, qg0[0], qg0[1], st0);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(cur, qg1[0], qg1[1], st1);
-    cur = nxt;
+    read_stat(0);
+    products(0, 0, false);
+    if (role == 0) probs(qt0, stat, xp[0][grp]);
+    else minus(stat);
+    int left = hpb * per_head, qt = qt0;
+    const auto interval = [&](auto stage) __attribute__((always_inline)) {
+      constexpr int b = decltype(stage)::value, bn = (b + 1) % kDkvStages;
+      wait_copies<(kDkvStages - 3) * kCopies>();
+      ring_barrier();
+      if (role == 1) grads(xp[b & 1][grp]);
+      __builtin_amdgcn_sched_barrier(0);
+      products(b, bn, true);
+      __builtin_amdgcn_sched_group_barrier(0x100, 3 * 2, 0);
+#pragma unroll
+      for (int i = 0; i < D / 16; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      read_stat(bn);
+      issue((b + kDkvStages - 1) % kDkvStages);     // under the last products
+      if (++qt == n_qt) qt = qt0;
+      if (role == 0) probs(qt, stat, xp[bn & 1][grp]);
+      else minus(stat);
+    };
+    while (true) {
+      interval(std::integral_constant<int, 0>{});
+      if (--left == 0) break;
+      interval(std::integral_constant<int, 1>{});
+      if (--left == 0) break;
+      interval(std::integral_constant<int, 2>{});
+      if (--left == 0) break;
+      interval(std::integral_constant<int, 3>{});
+      if (--left == 0) break;
+    }
+    wait_copies<0>();      // no copy may land after the end
   }
 
   if (!key_ok) return;
@@ -857,15 +964,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
   for (int i = 0; i < D / 32; ++i) dq[i] = f32x16{};
 
-  auto issue = [&](int seg, int t0, uint8_t* kt, uint8_t* vt) __attribute__((always_inline)) {
-    const KvSeg& s = p.seg[seg];
-    const int64_t off = bi * s.bstride + static_cast<int64_t>(t0) * s.ld + hk * D;
-    tile_load<D, KQ>(kt, s.k + off, s.ld, s.n - t0, wave, lane);
-    tile_load<D, KQ>(vt, s.v + off, s.ld, s.n - t0, wave, lane);
+  KeyWalk walk(p, pos_max, KQ, bi, hk * D);
+  const TileCopy<D, KQ> copy(p.seg[0].ld, wave, lane);
+  const uint32_t ka[2] = {lds_addr(k0), lds_addr(k1)}, va[2] = {lds_addr(v0), lds_addr(v1)};
+  auto issue = [&](Tile t, int b) __attribute__((always_inline)) {
+    copy(ka[b], walk.k(), t.kvalid);
+    copy(va[b], walk.v(), t.kvalid);
   };
-  auto compute = [&](int seg, int t0, const uint8_t* kt, const uint8_t* vt) __attribute__((always_inline)) {
-    const int kpos0 = p.seg[seg].pos0 + t0;
-    const int kvalid = min(KQ, p.seg[seg].n - t0);
+  auto compute = [&](Tile t, const uint8_t* kt, const uint8_t* vt) __attribute__((always_inline)) {
+    const int kpos0 = t.kpos0, kvalid = t.kvalid;
     f32x16 sc = f32x16{}, dp = f32x16{};
     scores2<D, kLookDq>(kt, 0, qf, sc, vt, 0, dof, dp, la);
     if (kpos0 + KQ - 1 > pos_min || kvalid < KQ) {      // tile straddles the diagonal (or is ragged)
@@ -879,16 +986,25 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
     const bf16x8 sf[2] = {frag_acc(sc, 0), frag_acc(sc, 8)};
     accum_t<D, 2, kLookDq>(kt, sf, dq, la);
   };
-  run_ring2(
-      p, pos_max, KQ,
-      [&](int seg, int t0, auto b) __attribute__((always_inline)) {
-        if constexpr (decltype(b)::value == 0) issue(seg, t0, k0, v0);
-        else issue(seg, t0, k1, v1);
-      },
-      [&](int seg, int t0, auto b) __attribute__((always_inline)) {
-        if constexpr (decltype(b)::value == 0) compute(seg, t0, k0, v0);
-        else compute(seg, t0, k1, v1);
-      });
+  // Two-stage copy ring: a tile is computed from one buffer pair while the next
+  // one lands in the other.
+  Tile t = walk.next();
+  if (t.kvalid) issue(t, 0);
+  while (t.kvalid) {
+    Tile t1 = walk.next();
+    wait_copies<0>();
+    ring_barrier();                      // every wave's copy is visible; the other buffers are free
+    if (t1.kvalid) issue(t1, 1);
+    __builtin_amdgcn_sched_barrier(0);   // the copies go out now, not next to the wait for them
+    compute(t, k0, v0);
+    if (!t1.kvalid) break;
+    t = walk.next();
+    wait_copies<0>();
+    ring_barrier();
+    if (t.kvalid) issue(t, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    compute(t1, k1, v1);
+  }
 
   if (!q_ok) return;
   constexpr int HALF_T = D / 64;

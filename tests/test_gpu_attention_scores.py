@@ -1,0 +1,53 @@
+"""The attention forward on its own stashed operands: ctx and the log-sum-exp of
+a layer call against float64 attention over the stashed Q, K, V, with scores of
+ordinary size and of a size where a row's maximum grows by many powers of two
+from tile to tile (the reference maximum of the online softmax may lag by 8),
+at sequence lengths around the 64-key and 128-query tiles and both head sizes.
+
+Bound: the products are exact in fp32 and P carries about 16 bits (2^-16 of
+sum P |V|, at most max |V|), so ctx is within one bf16 step (2^-8) of its value
+plus 2^-15 max |V|; the log-sum-exp, whose scores are fp32 sums, within 2^-18
+of the largest score plus 1e-5."""
+import math
+
+import pytest
+import torch
+
+import workloads as W
+from gpu_common import Buffers
+import paper_2411_06465_amd as L
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("scale", [1.0, 12.0])
+@pytest.mark.parametrize("d,seq,cp", [(64, 64, 1), (64, 193, 1), (128, 129, 1), (128, 520, 1), (128, 512, 2)])
+def test_forward_matches_float64_attention(d, seq, cp, scale):
+    print(f"\n[attention scores d={d} s={seq} cp={cp} scale={scale}]", flush=True)
+    w = W.LayerWorkload(f"scores-{d}-{seq}-{cp}", 4 * d, 4, 2, 256, seq, cp=cp, cp_rank=cp - 1, n_gpus=cp)
+    buf = Buffers(w)
+    buf.weights["qkv"].mul_(scale)
+    st = L.llama_layer_fwd(buf.model, buf.par, buf.weights, buf.x, buf.y, buf.arena, peers=buf.peers)
+    q, k, v, ctx = (buf.stash_view(st, n, (1, w.s_c, -1)).clone() for n in ("q", "k", "v", "ctx"))
+    lse = buf.stash_view(st, "lse", (1, 4, w.s_c), torch.float32).clone()
+    torch.cuda.synchronize()
+    st.release()
+    pos = torch.arange(seq).cuda()
+    rest = pos[:0]
+    if cp > 1:
+        n, own = seq // (2 * cp), (w.cp_rank, 2 * cp - 1 - w.cp_rank)
+        chunks = pos.view(2 * cp, n)
+        pos = torch.cat([chunks[i] for i in own])
+        rest = torch.cat([chunks[i] for i in range(2 * cp) if i not in own])
+        k = torch.cat([k, buf.peers["remote_k"].view(1, -1, k.shape[-1])], 1)
+        v = torch.cat([v, buf.peers["remote_v"].view(1, -1, v.shape[-1])], 1)
+    mask = torch.cat([pos, rest])[None] > pos[:, None]
+    for h in range(4):
+        qh, c = q[0, :, h * d:(h + 1) * d].double(), ctx[0, :, h * d:(h + 1) * d].double()
+        kh, vh = (t[0, :, h // 2 * d:(h // 2 + 1) * d].double() for t in (k, v))
+        s = (qh @ kh.T / math.sqrt(d)).masked_fill(mask, -math.inf)
+        ref = s.softmax(-1) @ vh
+        bound = 2.0 ** -8 * ref.abs() + 2.0 ** -15 * vh.abs().max()
+        assert bool(((c - ref).abs() <= bound).all()), (h, float(((c - ref).abs() / bound).max()))
+        big = float(s.masked_fill(mask, 0).abs().max())
+        assert float((lse[0, h].double() - s.logsumexp(-1)).abs().max()) <= 2.0 ** -18 * big + 1e-5
