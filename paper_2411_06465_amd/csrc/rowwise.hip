@@ -372,143 +372,168 @@ __global__ void rope_table_kernel(float2* tab, ChunkMap map, int32_t rows, int32
 }
 
 // ------------------------------------------------------------------ cross-entropy
-// One 256-thread block per token row of bf16 logits [n][v_t] (v_t % 8 == 0).
-// logits and dlogits may be the same buffer (the LM head overwrites the logits
-// with their gradient in place), so neither is declared __restrict__.
+// One block per token row of logits [n][v_t].  Both passes over a row (its
+// log-sum-exp; the softmax or the gradient) need all of it, so a block keeps the
+// row in registers where it fits, V 16-byte vectors per thread: the row is read
+// once, with all its loads in flight, and the kernel is bound by one read and
+// one write of the logits.  A row read twice came from memory twice: the rows of
+// the blocks in flight (32 MB per XCD at 32064 fp32 columns) are far more than
+// an L2 holds.  4096 fp32 rows of 32064 columns 287 -> 177 us (5.9 TB/s), 8192
+// bf16 rows 242 -> 188 us (5.6 TB/s).  Rows past 65536 columns are read twice.
 
-__global__ void __launch_bounds__(256) xent_rows_kernel(
+// (max, sum of exponentials relative to it) of every thread -> log of the row's
+// whole sum, combined with the other shards' log-sum-exp; stores the row's loss.
+// z_at(i): logit i of the row.
+template <int WAVES, typename Z>
+__device__ __forceinline__ float xent_lse(float mx, float se, int32_t v_t, int64_t v0, int64_t row,
+                                          const int64_t* __restrict__ targets, const float* __restrict__ peer_lse,
+                                          const float* __restrict__ peer_z, float* __restrict__ loss, Z&& z_at) {
+  __shared__ float red_m[WAVES], red_s[WAVES];
+  __shared__ float bcast;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // combine (max, sum) pairs across the wave, then the waves
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const float m2 = __shfl_xor(mx, o, 64), s2 = __shfl_xor(se, o, 64);
+    const float m = fmaxf(mx, m2);
+    se = (mx == -INFINITY ? 0.f : se * __expf(mx - m)) + (m2 == -INFINITY ? 0.f : s2 * __expf(m2 - m));
+    mx = m;
+  }
+  if (lane == 0) {
+    red_m[wave] = mx;
+    red_s[wave] = se;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float m = red_m[0];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) m = fmaxf(m, red_m[w]);
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) sum += red_m[w] == -INFINITY ? 0.f : red_s[w] * __expf(red_m[w] - m);
+    float lse = m + logf(sum);
+    if (peer_lse) {
+      const float p = peer_lse[row];
+      const float hi = fmaxf(lse, p), lo = fminf(lse, p);
+      lse = hi + log1pf(__expf(lo - hi));
+    }
+    const int64_t tgt = targets[row] - v0;
+    const float z = tgt >= 0 && tgt < v_t ? z_at(tgt) : peer_z ? peer_z[row] : 0.f;
+    loss[row] = lse - z;
+    bcast = lse;
+  }
+  __syncthreads();
+  return bcast;
+}
+
+// The running (max, sum) of a thread after eight, or four, more values.
+template <int N>
+__device__ __forceinline__ void xent_add(const float* f, float& mx, float& se) {
+  float m = f[0];
+#pragma unroll
+  for (int j = 1; j < N; ++j) m = fmaxf(m, f[j]);
+  if (m > mx) {
+    se *= __expf(mx - m);       // 0 while mx is -inf
+    mx = m;
+  }
+#pragma unroll
+  for (int j = 0; j < N; ++j) se += __expf(f[j] - mx);
+}
+__device__ __forceinline__ void xent_grad8(u32x4 v, int c, int64_t tgt, float lse, float grad_scale, u32x4* out) {
+  float f[8];
+  unpack8(v, f);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    float g = __expf(f[j] - lse);
+    if (c * 8 + j == tgt) g -= 1.0f;
+    f[j] = g * grad_scale;
+  }
+  out[c] = pack8(f);
+}
+
+// bf16 logits (v_t % 8 == 0): loss and gradient.  logits and dlogits may be the
+// same buffer (the LM head overwrites the logits with their gradient in place),
+// so neither is declared __restrict__.  V = 0: any row length, read twice.
+template <int THREADS, int V>
+__global__ void __launch_bounds__(THREADS) xent_rows_kernel(
     const uint16_t* logits, int32_t v_t, int64_t v0, const int64_t* __restrict__ targets,
     const float* __restrict__ peer_lse, const float* __restrict__ peer_z, float grad_scale,
     float* __restrict__ loss, uint16_t* dlogits) {
-  __shared__ float red_m[4], red_s[4];
-  __shared__ float bcast;
   const int64_t row = blockIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const u32x4* lr = reinterpret_cast<const u32x4*>(logits + row * v_t);
-  const int nch = v_t / 8;
-  // one read of the row: running maximum and the sum of exponentials relative to it
-  float mx = -INFINITY, se = 0.f;
-  for (int c = threadIdx.x; c < nch; c += 256) {
-    float f[8];
-    unpack8(lr[c], f);
-    float m8 = f[0];
-#pragma unroll
-    for (int j = 1; j < 8; ++j) m8 = fmaxf(m8, f[j]);
-    if (m8 > mx) {
-      se *= __expf(mx - m8);       // 0 while mx is -inf
-      mx = m8;
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) se += __expf(f[j] - mx);
-  }
-  // combine (max, sum) pairs across the wave, then the four waves
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float m2 = __shfl_xor(mx, o, 64), s2 = __shfl_xor(se, o, 64);
-    const float m = fmaxf(mx, m2);
-    se = (mx == -INFINITY ? 0.f : se * __expf(mx - m)) + (m2 == -INFINITY ? 0.f : s2 * __expf(m2 - m));
-    mx = m;
-  }
-  if (lane == 0) {
-    red_m[wave] = mx;
-    red_s[wave] = se;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float m = fmaxf(fmaxf(red_m[0], red_m[1]), fmaxf(red_m[2], red_m[3]));
-    float sum = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) sum += red_m[w] == -INFINITY ? 0.f : red_s[w] * __expf(red_m[w] - m);
-    float lse = m + logf(sum);
-    if (peer_lse) {
-      const float p = peer_lse[row];
-      const float hi = fmaxf(lse, p), lo = fminf(lse, p);
-      lse = hi + log1pf(__expf(lo - hi));
-    }
-    const int64_t tgt = targets[row] - v0;
-    float z;
-    if (tgt >= 0 && tgt < v_t) z = __uint_as_float(static_cast<uint32_t>(logits[row * v_t + tgt]) << 16);
-    else z = peer_z ? peer_z[row] : 0.f;
-    loss[row] = lse - z;
-    bcast = lse;
-  }
-  __syncthreads();
-  const float lse = bcast;
-  const int64_t tgt = targets[row] - v0;
   u32x4* dr = reinterpret_cast<u32x4*>(dlogits + row * v_t);
-  for (int c = threadIdx.x; c < nch; c += 256) {
-    float f[8];
-    unpack8(lr[c], f);
+  const int nch = v_t / 8;
+  float mx = -INFINITY, se = 0.f;
+  auto z_at = [&](int64_t i) { return __uint_as_float(static_cast<uint32_t>(logits[row * v_t + i]) << 16); };
+  const int64_t tgt = targets[row] - v0;
+  if constexpr (V > 0) {
+    u32x4 v[V];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      float g = __expf(f[j] - lse);
-      if (c * 8 + j == tgt) g -= 1.0f;
-      f[j] = g * grad_scale;
+    for (int q = 0; q < V; ++q) {
+      const int c = q * THREADS + threadIdx.x;
+      v[q] = lr[min(c, nch - 1)];
     }
-    dr[c] = pack8(f);
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+      float f[8];
+      unpack8(v[q], f);
+      if (q * THREADS + static_cast<int>(threadIdx.x) < nch) xent_add<8>(f, mx, se);
+    }
+    const float lse = xent_lse<THREADS / 64>(mx, se, v_t, v0, row, targets, peer_lse, peer_z, loss, z_at);
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+      const int c = q * THREADS + threadIdx.x;
+      if (c < nch) xent_grad8(v[q], c, tgt, lse, grad_scale, dr);
+    }
+  } else {
+    for (int c = threadIdx.x; c < nch; c += THREADS) {
+      float f[8];
+      unpack8(lr[c], f);
+      xent_add<8>(f, mx, se);
+    }
+    const float lse = xent_lse<THREADS / 64>(mx, se, v_t, v0, row, targets, peer_lse, peer_z, loss, z_at);
+    for (int c = threadIdx.x; c < nch; c += THREADS) xent_grad8(lr[c], c, tgt, lse, grad_scale, dr);
   }
 }
 
-
-// FP32 logits [n][v_t] (v_t % 4 == 0), one 256-thread block per row: the loss,
-// and the row overwritten with the softmax exp(z - LSE) over the whole
-// vocabulary (LSE combined with the other shards' log-sum-exp).
-__global__ void __launch_bounds__(256) xent_probs_kernel(
+// FP32 logits (v_t % 4 == 0): the loss, and the row overwritten with the softmax
+// exp(z - LSE) over the whole vocabulary.
+template <int THREADS, int V>
+__global__ void __launch_bounds__(THREADS) xent_probs_kernel(
     float* __restrict__ lp, int32_t v_t, int64_t v0, const int64_t* __restrict__ targets,
     const float* __restrict__ peer_lse, const float* __restrict__ peer_z, float* __restrict__ loss) {
-  __shared__ float red_m[4], red_s[4];
-  __shared__ float bcast;
   const int64_t row = blockIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float4* r4 = reinterpret_cast<float4*>(lp + row * v_t);
+  f32x4* r4 = reinterpret_cast<f32x4*>(lp + row * v_t);
   const int nch = v_t / 4;
-  // one pass: running maximum and the sum of exponentials relative to it
   float mx = -INFINITY, se = 0.f;
-  for (int c = threadIdx.x; c < nch; c += 256) {
-    const float4 f = r4[c];
-    const float m4 = fmaxf(fmaxf(f.x, f.y), fmaxf(f.z, f.w));
-    if (m4 > mx) {
-      se *= __expf(mx - m4);       // 0 while mx is -inf
-      mx = m4;
-    }
-    se += __expf(f.x - mx) + __expf(f.y - mx) + __expf(f.z - mx) + __expf(f.w - mx);
-  }
-  // combine (max, sum) pairs across the wave, then the four waves
+  auto z_at = [&](int64_t i) { return lp[row * v_t + i]; };
+  auto put = [&](f32x4 f, int c, float lse) {
+    r4[c] = f32x4{__expf(f[0] - lse), __expf(f[1] - lse), __expf(f[2] - lse), __expf(f[3] - lse)};
+  };
+  auto add = [&](f32x4 v) {
+    const float f[4] = {v[0], v[1], v[2], v[3]};
+    xent_add<4>(f, mx, se);
+  };
+  if constexpr (V > 0) {
+    f32x4 v[V];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float m2 = __shfl_xor(mx, o, 64), s2 = __shfl_xor(se, o, 64);
-    const float m = fmaxf(mx, m2);
-    se = (mx == -INFINITY ? 0.f : se * __expf(mx - m)) + (m2 == -INFINITY ? 0.f : s2 * __expf(m2 - m));
-    mx = m;
-  }
-  if (lane == 0) {
-    red_m[wave] = mx;
-    red_s[wave] = se;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float m = fmaxf(fmaxf(red_m[0], red_m[1]), fmaxf(red_m[2], red_m[3]));
-    float sum = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) sum += red_m[w] == -INFINITY ? 0.f : red_s[w] * __expf(red_m[w] - m);
-    float lse = m + logf(sum);
-    if (peer_lse) {
-      const float p = peer_lse[row];
-      const float hi = fmaxf(lse, p), lo = fminf(lse, p);
-      lse = hi + log1pf(__expf(lo - hi));
+    for (int q = 0; q < V; ++q) {
+      const int c = q * THREADS + threadIdx.x;
+      v[q] = r4[min(c, nch - 1)];
     }
-    const int64_t tgt = targets[row] - v0;
-    float z;
-    if (tgt >= 0 && tgt < v_t) z = lp[row * v_t + tgt];
-    else z = peer_z ? peer_z[row] : 0.f;
-    loss[row] = lse - z;
-    bcast = lse;
-  }
-  __syncthreads();
-  const float lse = bcast;
-  for (int c = threadIdx.x; c < nch; c += 256) {
-    const float4 f = r4[c];
-    r4[c] = make_float4(__expf(f.x - lse), __expf(f.y - lse), __expf(f.z - lse), __expf(f.w - lse));
+#pragma unroll
+    for (int q = 0; q < V; ++q)
+      if (q * THREADS + static_cast<int>(threadIdx.x) < nch) add(v[q]);
+    const float lse = xent_lse<THREADS / 64>(mx, se, v_t, v0, row, targets, peer_lse, peer_z, loss, z_at);
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+      const int c = q * THREADS + threadIdx.x;
+      if (c < nch) put(v[q], c, lse);
+    }
+  } else {
+    for (int c = threadIdx.x; c < nch; c += THREADS) add(r4[c]);
+    const float lse = xent_lse<THREADS / 64>(mx, se, v_t, v0, row, targets, peer_lse, peer_z, loss, z_at);
+    for (int c = threadIdx.x; c < nch; c += THREADS) put(r4[c], c, lse);
   }
 }
 
@@ -755,16 +780,30 @@ hipError_t xent_rows(const uint16_t* logits, int64_t n, int32_t v_t, int64_t v0,
                      const float* peer_lse, const float* peer_z, float grad_scale, float* loss,
                      uint16_t* dlogits, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(xent_rows_kernel, dim3(static_cast<unsigned>(n)), dim3(256), 0, stream, logits, v_t, v0,
-                     targets, peer_lse, peer_z, grad_scale, loss, dlogits);
+  // the fewest threads whose registers hold the row, up to 1024
+  const dim3 grid(static_cast<unsigned>(n));
+  auto go = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, logits, v_t, v0, targets, peer_lse, peer_z, grad_scale,
+                       loss, dlogits);
+  };
+  if (v_t <= 256 * 4 * 8) go(xent_rows_kernel<256, 4>, 256);
+  else if (v_t <= 512 * 8 * 8) go(xent_rows_kernel<512, 8>, 512);
+  else if (v_t <= 1024 * 8 * 8) go(xent_rows_kernel<1024, 8>, 1024);
+  else go(xent_rows_kernel<256, 0>, 256);
   return hipGetLastError();
 }
 
 hipError_t xent_probs(float* logits, int64_t n, int32_t v_t, int64_t v0, const int64_t* targets,
                       const float* peer_lse, const float* peer_z, float* loss, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(xent_probs_kernel, dim3(static_cast<unsigned>(n)), dim3(256), 0, stream, logits, v_t, v0,
-                     targets, peer_lse, peer_z, loss);
+  const dim3 grid(static_cast<unsigned>(n));
+  auto go = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, logits, v_t, v0, targets, peer_lse, peer_z, loss);
+  };
+  if (v_t <= 256 * 8 * 4) go(xent_probs_kernel<256, 8>, 256);
+  else if (v_t <= 1024 * 8 * 4) go(xent_probs_kernel<1024, 8>, 1024);
+  else if (v_t <= 1024 * 16 * 4) go(xent_probs_kernel<1024, 16>, 1024);
+  else go(xent_probs_kernel<256, 0>, 256);
   return hipGetLastError();
 }
 
