@@ -801,12 +801,11 @@ extern "C" int llama_layer_fwd(const l4d_model* m, const l4d_parallel* p, const 
 
   auto body = [&]() -> int {
     int r;
-    if ((r = launch("rope_table", s, [&] { return rope_table(rope, x.qmap, (int32_t)x.s_c, (int32_t)x.d, x.base, s); })))
-      return r;
-    // norm-1, stashing its input x as it goes
+    const RopeTable table{rope, x.qmap, (int32_t)x.s_c, (int32_t)x.d, std::log((double)x.base)};
+    // norm-1, stashing its input x as it goes, and the RoPE table
     if ((r = launch("rmsnorm1_fwd", s, [&] {
            return rmsnorm_fwd(static_cast<const uint16_t*>(x_in), static_cast<const uint16_t*>(w->norm1),
-                              sptr(st, L4D_STASH_XN1), x.b * x.s_sp, (int32_t)x.h, x.eps, s, sptr(st, L4D_STASH_X));
+                              sptr(st, L4D_STASH_XN1), x.b * x.s_sp, (int32_t)x.h, x.eps, s, sptr(st, L4D_STASH_X), &table);
          })))
       return r;
     // [Q|K|V] = xn1_full W_qkv^T, RoPE on Q, K
@@ -914,8 +913,7 @@ extern "C" int llama_layer_bwd(const l4d_model* m, const l4d_parallel* p, const 
 
   auto body = [&]() -> int {
     int r;
-    if ((r = launch("rope_table", s, [&] { return rope_table(rope, x.qmap, (int32_t)x.s_c, (int32_t)x.d, x.base, s); })))
-      return r;
+    const RopeTable table{rope, x.qmap, (int32_t)x.s_c, (int32_t)x.d, std::log((double)x.base)};
     const RowSrc dy_full = gathered(dy, pi.sp_peer_dy, x);
     // d(prod) = dy_full W_down, consumed by the SwiGLU backward in the epilogue
     EpiParams es{};
@@ -948,7 +946,8 @@ extern "C" int llama_layer_bwd(const l4d_model* m, const l4d_parallel* p, const 
                               rows_sp, (int32_t)x.h, x.eps, s);
          })))
       return r;
-    if ((r = launch("reduce_gain", s, [&] { return reduce_rows_add(partial, npart, (int32_t)x.h, dw->norm2, s); })))
+    // the gain gradient's sum, and the RoPE table for the attention backward
+    if ((r = launch("reduce_gain", s, [&] { return reduce_rows_add(partial, npart, (int32_t)x.h, dw->norm2, s, &table); })))
       return r;
     // attention output projection
     const RowSrc dh1_full = gathered(dh1, pi.sp_peer_dh1, x);

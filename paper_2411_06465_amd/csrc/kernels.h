@@ -127,10 +127,24 @@ hipError_t gemm_split_store(uint16_t* c, int64_t ldc, const float* partial, int6
 
 // ---------------------------------------------------------------- row-wise kernels
 
+// cos/sin table for RoPE: tab[i][j] = (cos, sin)(pos_i * base^(-2j/d_h)), computed in fp64.
+struct ChunkMap {          // local row -> global position
+  int32_t n_chunks;        // 1 or 2
+  int32_t chunk_len;
+  int32_t chunk_id[2];
+};
+struct RopeTable {         // a table to fill: rows x d_h/2 entries
+  float2* tab;
+  ChunkMap map;
+  int32_t rows, d_h;
+  double log_base;         // log(base)
+};
+
 // y = bf16(gain * x * rsqrt(mean(x^2) + eps)), one row of h per wave; x is
 // also copied to x_copy when that is not null.
 hipError_t rmsnorm_fwd(const uint16_t* x, const uint16_t* gain, uint16_t* y, int64_t rows,
-                       int32_t h, float eps, hipStream_t stream, uint16_t* x_copy = nullptr);
+                       int32_t h, float eps, hipStream_t stream, uint16_t* x_copy = nullptr,
+                       const RopeTable* rope = nullptr);
 // RMSNorm backward: dx = dres + d rmsnorm/dx . dy, stored bf16 (and fp32 when
 // dx_f32 is set);  partial[blk][h] = sum over the block's rows of dy*xhat.
 // dy is bf16 (dy) or fp32 (dy_f32); dres is absent, bf16 or fp32.  Forms:
@@ -147,17 +161,9 @@ hipError_t rmsnorm_bwd(const uint16_t* x, const uint16_t* gain, const NormBwdIo&
                        int32_t n_partial, int64_t rows, int32_t h, float eps, hipStream_t stream);
 // out[j] += sum_i partial[i][j] in a fixed order; with more than 256 rows partial
 // is overwritten (used as scratch).
-hipError_t reduce_rows_add(float* partial, int32_t n_partial, int32_t h, float* out, hipStream_t stream);
+hipError_t reduce_rows_add(const float* partial, int32_t n_partial, int32_t h, float* out, hipStream_t stream,
+                           const RopeTable* rope = nullptr);
 int32_t rmsnorm_bwd_partials(int64_t rows);
-
-// cos/sin table for RoPE: tab[i][j] = (cos, sin)(pos_i * base^(-2j/d_h)), computed in fp64.
-struct ChunkMap {          // local row -> global position
-  int32_t n_chunks;        // 1 or 2
-  int32_t chunk_len;
-  int32_t chunk_id[2];
-};
-hipError_t rope_table(float2* tab, ChunkMap map, int32_t rows, int32_t d_h, float base,
-                      hipStream_t stream);
 
 // ---------------------------------------------------------------- attention
 

@@ -38,21 +38,52 @@ __device__ __forceinline__ float wave_sum(float v) {
 
 constexpr int kMaxChunks = 16;   // h <= 64 lanes * 16 chunks * 8 = 8192
 
+// ------------------------------------------------------------------ RoPE table
+
+// Entry idx of the cos/sin table.  The table has no launch of its own: its
+// entries are extra blocks of a kernel that runs ahead of the first reader anyway
+// (the first norm in the forward, the second norm's gain sum in the backward),
+// where double-precision work on a few CUs hides beside the rows; alone it cost
+// 3 (16 blocks) to 5 us (2048 blocks) a pass.
+__device__ __forceinline__ void rope_entry(const RopeTable& r, int64_t idx) {
+  const int half = r.d_h / 2;
+  if (idx >= static_cast<int64_t>(r.rows) * half) return;
+  const int i = static_cast<int>(idx / half), j = static_cast<int>(idx % half);
+  const int ci = i / r.map.chunk_len;
+  const int64_t pos = static_cast<int64_t>(r.map.chunk_id[ci]) * r.map.chunk_len + (i - ci * r.map.chunk_len);
+  const double ang = static_cast<double>(pos) * exp(-2.0 * j / r.d_h * r.log_base);
+  double s, c;
+  sincos(ang, &s, &c);
+  r.tab[idx] = make_float2(static_cast<float>(c), static_cast<float>(s));
+}
+unsigned rope_blocks(const RopeTable* r, int threads) {
+  return r ? static_cast<unsigned>((static_cast<int64_t>(r->rows) * (r->d_h / 2) + threads - 1) / threads) : 0u;
+}
+
 // ------------------------------------------------------------------ RMSNorm
 
 // One wave per row.  All of the row's loads are issued before the first use,
 // so that a wave keeps its whole row (8 KB at h = 4096) in flight: a use right
 // after each load waits for it and leaves one kilobyte in flight per wave.
 // CPT > 0: h = 512 CPT (every lane holds CPT chunks, no bounds); CPT = 0: any
-// h that is a multiple of 8.
-template <int CPT>
+// h that is a multiple of 8.  ROPE: the first rope_blk blocks fill the RoPE table.
+template <int CPT, bool ROPE>
 __global__ void __launch_bounds__(256) rmsnorm_fwd_kernel(const uint16_t* __restrict__ x,
                                                           const uint16_t* __restrict__ gain,
                                                           uint16_t* __restrict__ y, uint16_t* __restrict__ x_copy,
-                                                          int64_t rows, int32_t h, float eps) {
+                                                          int64_t rows, int32_t h, float eps, RopeTable rope,
+                                                          int32_t rope_blk) {
   constexpr int NC = CPT > 0 ? CPT : kMaxChunks;
   const int lane = threadIdx.x & 63;
-  const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+  int64_t block = blockIdx.x;
+  if constexpr (ROPE) {
+    if (block < rope_blk) {
+      rope_entry(rope, block * 256 + threadIdx.x);
+      return;
+    }
+    block -= rope_blk;
+  }
+  const int64_t row = block * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
   const int nch = CPT > 0 ? 64 * CPT : h / 8;
   const u32x4* xr = reinterpret_cast<const u32x4*>(x + row * h);
@@ -296,79 +327,44 @@ __global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(
   }
 }
 
-// Column sums of partial[n][h] in two deterministic levels (no atomics):
-// level 1 sums each slice of 64 rows into the slice's first row, in place,
-// a block per (64 columns, slice) with its 4 waves taking every 4th row;
-// level 2 adds the slice sums, in slice order, into out.
-__global__ void __launch_bounds__(256) reduce_slices_kernel(float* __restrict__ partial, int32_t n, int32_t h) {
-  __shared__ float s4[4][64];
+// out += the column sums of partial[n][h], n <= 256, in a fixed order (no
+// atomics): a block of 16 waves per 64 columns, wave w taking rows w, w + 16, ..,
+// all their loads in flight at once, since the kernel's time is the latency of
+// its loads (128 rows of 256 columns 4.0 -> 2.0 us, 256 rows of 2048 to 8192
+// columns 7 -> 4.7 us against 4 waves with 4 loads in flight each).  ROPE: the blocks past the columns fill the RoPE table.
+constexpr int kSumWaves = 16, kSumRows = 256 / kSumWaves;
+template <bool ROPE>
+__global__ void __launch_bounds__(kSumWaves * 64) column_sums_kernel(const float* __restrict__ partial, int32_t n,
+                                                                     int32_t h, float* __restrict__ out,
+                                                                     RopeTable rope) {
+  if constexpr (ROPE) {
+    const int col_blk = (h + 63) / 64, blk = static_cast<int>(blockIdx.x) - col_blk;
+    if (blk >= 0) {
+      rope_entry(rope, static_cast<int64_t>(blk) * (kSumWaves * 64) + threadIdx.x);
+      return;
+    }
+  }
+  __shared__ float sums[kSumWaves][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = blockIdx.x * 64 + lane;
-  const int r0 = blockIdx.y * 64, r1 = min(r0 + 64, n);
-  float s = 0.f;
-  if (col < h) {
-    int i = r0 + wave;
-    for (; i + 12 < r1; i += 16) {     // four independent loads in flight
-      const float a = partial[static_cast<int64_t>(i) * h + col];
-      const float b = partial[static_cast<int64_t>(i + 4) * h + col];
-      const float c = partial[static_cast<int64_t>(i + 8) * h + col];
-      const float d = partial[static_cast<int64_t>(i + 12) * h + col];
-      s += (a + b) + (c + d);
-    }
-    for (; i < r1; i += 4) s += partial[static_cast<int64_t>(i) * h + col];
+  float v[kSumRows];
+#pragma unroll
+  for (int i = 0; i < kSumRows; ++i) {
+    const int r = wave + kSumWaves * i;
+    v[i] = r < n && col < h ? partial[static_cast<int64_t>(r) * h + col] : 0.f;
   }
-  s4[wave][lane] = s;
+#pragma unroll
+  for (int d = kSumRows / 2; d > 0; d /= 2)
+#pragma unroll
+    for (int i = 0; i < d; ++i) v[i] += v[i + d];
+  sums[wave][lane] = v[0];
   __syncthreads();
-  if (wave == 0 && col < h)
-    partial[static_cast<int64_t>(r0) * h + col] = (s4[0][lane] + s4[1][lane]) + (s4[2][lane] + s4[3][lane]);
-}
-
-// One level for at most 256 partial rows: a block per 64 columns, its 4 waves
-// taking every 4th row (four loads in flight each), then out += the column sums.
-__global__ void __launch_bounds__(256) reduce_all_kernel(const float* __restrict__ partial, int32_t n, int32_t h,
-                                                        float* __restrict__ out) {
-  __shared__ float s4[4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col = blockIdx.x * 64 + lane;
-  float s = 0.f;
-  if (col < h) {
-    int i = wave;
-    for (; i + 12 < n; i += 16) {
-      const float a = partial[static_cast<int64_t>(i) * h + col];
-      const float b = partial[static_cast<int64_t>(i + 4) * h + col];
-      const float c = partial[static_cast<int64_t>(i + 8) * h + col];
-      const float d = partial[static_cast<int64_t>(i + 12) * h + col];
-      s += (a + b) + (c + d);
-    }
-    for (; i < n; i += 4) s += partial[static_cast<int64_t>(i) * h + col];
+  if (wave == 0 && col < h) {
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < kSumWaves; ++w) s += sums[w][lane];
+    out[col] += s;
   }
-  s4[wave][lane] = s;
-  __syncthreads();
-  if (wave == 0 && col < h) out[col] += (s4[0][lane] + s4[1][lane]) + (s4[2][lane] + s4[3][lane]);
-}
-
-__global__ void __launch_bounds__(256) add_slices_kernel(const float* __restrict__ partial, int32_t n_slices,
-                                                         int32_t h, float* __restrict__ out) {
-  const int col = blockIdx.x * 256 + threadIdx.x;
-  if (col >= h) return;
-  float s = 0.f;
-  for (int i = 0; i < n_slices; ++i) s += partial[static_cast<int64_t>(i) * 64 * h + col];
-  out[col] += s;
-}
-
-// ------------------------------------------------------------------ RoPE table
-
-__global__ void rope_table_kernel(float2* tab, ChunkMap map, int32_t rows, int32_t d_h, double log_base) {
-  const int half = d_h / 2;
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (idx >= static_cast<int64_t>(rows) * half) return;
-  const int i = static_cast<int>(idx / half), j = static_cast<int>(idx % half);
-  const int ci = i / map.chunk_len;
-  const int64_t pos = static_cast<int64_t>(map.chunk_id[ci]) * map.chunk_len + (i - ci * map.chunk_len);
-  const double ang = static_cast<double>(pos) * exp(-2.0 * j / d_h * log_base);
-  double s, c;
-  sincos(ang, &s, &c);
-  tab[idx] = make_float2(static_cast<float>(c), static_cast<float>(s));
 }
 
 // ------------------------------------------------------------------ cross-entropy
@@ -712,13 +708,18 @@ __global__ void __launch_bounds__(256) embed_bwd_kernel(const int64_t* __restric
 }  // namespace
 
 hipError_t rmsnorm_fwd(const uint16_t* x, const uint16_t* gain, uint16_t* y, int64_t rows, int32_t h,
-                       float eps, hipStream_t stream, uint16_t* x_copy) {
+                       float eps, hipStream_t stream, uint16_t* x_copy, const RopeTable* rope) {
   if (rows <= 0) return hipSuccess;
-  const dim3 grid(static_cast<unsigned>((rows + 3) / 4));
+  const unsigned rope_blk = rope_blocks(rope, 256);
+  const dim3 grid(static_cast<unsigned>((rows + 3) / 4) + rope_blk);
+  auto go = [&](auto with_rope, auto without) {
+    hipLaunchKernelGGL(rope ? with_rope : without, grid, dim3(256), 0, stream, x, gain, y, x_copy, rows, h, eps,
+                       rope ? *rope : RopeTable{}, static_cast<int32_t>(rope_blk));
+  };
   switch (h % 512 == 0 ? h / 512 : 0) {
-    case 8: hipLaunchKernelGGL(rmsnorm_fwd_kernel<8>, grid, dim3(256), 0, stream, x, gain, y, x_copy, rows, h, eps); break;
-    case 16: hipLaunchKernelGGL(rmsnorm_fwd_kernel<16>, grid, dim3(256), 0, stream, x, gain, y, x_copy, rows, h, eps); break;
-    default: hipLaunchKernelGGL(rmsnorm_fwd_kernel<0>, grid, dim3(256), 0, stream, x, gain, y, x_copy, rows, h, eps);
+    case 8: go(rmsnorm_fwd_kernel<8, true>, rmsnorm_fwd_kernel<8, false>); break;
+    case 16: go(rmsnorm_fwd_kernel<16, true>, rmsnorm_fwd_kernel<16, false>); break;
+    default: go(rmsnorm_fwd_kernel<0, true>, rmsnorm_fwd_kernel<0, false>);
   }
   return hipGetLastError();
 }
@@ -757,22 +758,13 @@ hipError_t rmsnorm_bwd(const uint16_t* x, const uint16_t* gain, const NormBwdIo&
   return hipGetLastError();
 }
 
-hipError_t reduce_rows_add(float* partial, int32_t n_partial, int32_t h, float* out, hipStream_t stream) {
+hipError_t reduce_rows_add(const float* partial, int32_t n_partial, int32_t h, float* out, hipStream_t stream,
+                           const RopeTable* rope) {
+  if (n_partial > 256) return hipErrorInvalidValue;      // rmsnorm_bwd_partials gives at most 256
   if (n_partial <= 0) return hipSuccess;
-  if (n_partial <= 256) {
-    hipLaunchKernelGGL(reduce_all_kernel, dim3((h + 63) / 64), dim3(256), 0, stream, partial, n_partial, h, out);
-    return hipGetLastError();
-  }
-  const int slices = (n_partial + 63) / 64;
-  hipLaunchKernelGGL(reduce_slices_kernel, dim3((h + 63) / 64, slices), dim3(256), 0, stream, partial, n_partial, h);
-  hipLaunchKernelGGL(add_slices_kernel, dim3((h + 255) / 256), dim3(256), 0, stream, partial, slices, h, out);
-  return hipGetLastError();
-}
-
-hipError_t rope_table(float2* tab, ChunkMap map, int32_t rows, int32_t d_h, float base, hipStream_t stream) {
-  const int64_t n = static_cast<int64_t>(rows) * (d_h / 2);
-  hipLaunchKernelGGL(rope_table_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, stream,
-                     tab, map, rows, d_h, log(static_cast<double>(base)));
+  const dim3 grid(static_cast<unsigned>((h + 63) / 64) + rope_blocks(rope, kSumWaves * 64));
+  hipLaunchKernelGGL(rope ? column_sums_kernel<true> : column_sums_kernel<false>, grid, dim3(kSumWaves * 64), 0, stream,
+                     partial, n_partial, h, out, rope ? *rope : RopeTable{});
   return hipGetLastError();
 }
 
