@@ -1179,8 +1179,14 @@ extern "C" int embedding_bwd(const l4d_model* m, const l4d_parallel* p, l4d_stas
   if (!dx || !d_w_emb) return fail(L4D_EINVAL, "dx and d_w_emb are required");
   if ((x.t > 1) != (peer_dx != nullptr)) return fail(L4D_EINVAL, "peer_dx is required iff tp > 1");
   hipStream_t s = static_cast<hipStream_t>(stream_ptr);
+  // the sorted tokens; an arena without room for them still runs the call, unsorted
+  Workspace ws;
+  ws.A = A;
+  ws.size = align_up(embed_bwd_ws_bytes(x.b * x.s_c));
+  ws.held = ws.size && arena_alloc(A, ws.size, &ws.off);
+  uint64_t* keys = ws.held ? reinterpret_cast<uint64_t*>(A->base + ws.off) : nullptr;
   if ((rc = launch("embed_bwd", s, [&] {
-         return embed_bwd(sptr<int64_t>(st, L4D_EMB_IDS), gathered(dx, peer_dx, x), v0, (int32_t)v_t,
+         return embed_bwd(sptr<const int64_t>(st, L4D_EMB_IDS), keys, gathered(dx, peer_dx, x), v0, (int32_t)v_t,
                           (int32_t)x.h, x.b * x.s_c, d_w_emb, s);
        })))
     return rc;

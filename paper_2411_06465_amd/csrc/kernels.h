@@ -159,8 +159,7 @@ struct NormBwdIo {
 };
 hipError_t rmsnorm_bwd(const uint16_t* x, const uint16_t* gain, const NormBwdIo& io, float* partial,
                        int32_t n_partial, int64_t rows, int32_t h, float eps, hipStream_t stream);
-// out[j] += sum_i partial[i][j] in a fixed order; with more than 256 rows partial
-// is overwritten (used as scratch).
+// out[j] += sum_i partial[i][j], at most 256 rows, in a fixed order.
 hipError_t reduce_rows_add(const float* partial, int32_t n_partial, int32_t h, float* out, hipStream_t stream,
                            const RopeTable* rope = nullptr);
 int32_t rmsnorm_bwd_partials(int64_t rows);
@@ -245,10 +244,12 @@ hipError_t xent_grad(const float* probs, int64_t n, int32_t v_t, int64_t v0, con
 hipError_t embed_fwd(const int64_t* ids, const uint16_t* w, int64_t v0, int32_t v_t, int32_t h, int64_t rows,
                      int32_t s_c, int32_t s_sp, int32_t r, int32_t t, const uint16_t* receipt, uint16_t* own,
                      uint16_t* send, int64_t* kept, hipStream_t stream);
-// dw[ids[m] - v0] += dy.row(m) for the ids in range (fp32 atomics).  ids is
-// overwritten (sorted in place).
-hipError_t embed_bwd(int64_t* ids, RowSrc dy, int64_t v0, int32_t v_t, int32_t h, int64_t rows, float* dw,
-                     hipStream_t stream);
+// dw[ids[m] - v0] += dy.row(m) for the ids in range (fp32 atomics).  keys:
+// embed_bwd_ws_bytes(rows) bytes in which the tokens are sorted by id, or NULL =
+// added in token order (slower where ids repeat).
+uint64_t embed_bwd_ws_bytes(int64_t rows);
+hipError_t embed_bwd(const int64_t* ids, uint64_t* keys, RowSrc dy, int64_t v0, int32_t v_t, int32_t h, int64_t rows,
+                     float* dw, hipStream_t stream);
 
 // ---------------------------------------------------------------- optimizer
 

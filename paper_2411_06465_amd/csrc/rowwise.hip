@@ -607,18 +607,20 @@ __global__ void __launch_bounds__(256) embed_fwd_kernel(const int64_t* __restric
 // One atomic row per token was bound by the atomics: a few ids repeat often in
 // text, so their rows were added one after another at the same addresses, and
 // a lane's 8 consecutive columns spread every atomic instruction over 16 cache
-// lines.  Now chunks of kEmbChunk tokens are sorted by id (embed_sort, in the
-// stashed ids, which the backward consumes), a workgroup walks a window of
-// kEmbWin sorted tokens over 1024 columns and adds each run of equal ids up in
-// registers before one atomic add per column, consecutive lanes on consecutive
-// columns.  8192 tokens of hidden 4096 over a shard of 32064 (heavy-tailed ids,
+// lines.  Now chunks of kEmbChunk tokens are sorted by id (embed_sort, into
+// workspace: the stashed ids stay, so a captured backward can be replayed), a
+// workgroup walks a window of kEmbWin sorted tokens over 1024 columns and adds
+// each run of equal ids up in registers before one atomic add per column,
+// consecutive lanes on consecutive columns.  8192 tokens of hidden 4096 over a shard of 32064 (heavy-tailed ids,
 // a quarter of them in the shard): 627 -> 15 (sort) + 28 us.
 constexpr int kEmbChunk = 2048, kEmbWin = 16;
 
 // Keys (id - v0) << 32 | token, out-of-range ids as all ones, sorted ascending
-// per chunk in place: a bitonic network over LDS (66 steps, one exchange per
+// per chunk: a bitonic network over LDS (66 steps, one exchange per
 // thread and step).
-__global__ void __launch_bounds__(kEmbChunk / 2) embed_sort_kernel(uint64_t* keys, int64_t v0, int32_t v_t, int64_t n) {
+__global__ void __launch_bounds__(kEmbChunk / 2) embed_sort_kernel(const int64_t* __restrict__ ids,
+                                                                  uint64_t* __restrict__ keys, int64_t v0, int32_t v_t,
+                                                                  int64_t n) {
   __shared__ uint64_t k[kEmbChunk];
   const int tid = threadIdx.x;
   const int64_t base = static_cast<int64_t>(blockIdx.x) * kEmbChunk;
@@ -626,7 +628,7 @@ __global__ void __launch_bounds__(kEmbChunk / 2) embed_sort_kernel(uint64_t* key
   for (int i = tid; i < kEmbChunk; i += kEmbChunk / 2) {
     uint64_t key = ~0ull;
     if (base + i < n) {
-      const int64_t j = static_cast<int64_t>(keys[base + i]) - v0;
+      const int64_t j = ids[base + i] - v0;
       if (j >= 0 && j < v_t) key = static_cast<uint64_t>(j) << 32 | static_cast<uint32_t>(base + i);
     }
     k[i] = key;
@@ -817,18 +819,21 @@ hipError_t embed_fwd(const int64_t* ids, const uint16_t* w, int64_t v0, int32_t 
   return hipGetLastError();
 }
 
-hipError_t embed_bwd(int64_t* ids, RowSrc dy, int64_t v0, int32_t v_t, int32_t h, int64_t rows, float* dw,
-                     hipStream_t stream) {
+// Few tokens share few ids, and the sort would cost a launch of its own.
+uint64_t embed_bwd_ws_bytes(int64_t rows) { return rows <= 512 ? 0 : static_cast<uint64_t>(rows) * 8; }
+
+hipError_t embed_bwd(const int64_t* ids, uint64_t* keys, RowSrc dy, int64_t v0, int32_t v_t, int32_t h, int64_t rows,
+                     float* dw, hipStream_t stream) {
   if (rows <= 0) return hipSuccess;
   const dim3 grid(static_cast<unsigned>((rows + kEmbWin - 1) / kEmbWin), static_cast<unsigned>((h + 1023) / 1024));
-  // few tokens share few ids, and the sort would cost a launch of its own
-  if (rows <= 512) {
+  if (!keys) {
     hipLaunchKernelGGL(embed_bwd_kernel<false>, grid, dim3(256), 0, stream, ids, dy, v0, v_t, h, rows, dw);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(embed_sort_kernel, dim3(static_cast<unsigned>((rows + kEmbChunk - 1) / kEmbChunk)),
-                     dim3(kEmbChunk / 2), 0, stream, reinterpret_cast<uint64_t*>(ids), v0, v_t, rows);
-  hipLaunchKernelGGL(embed_bwd_kernel<true>, grid, dim3(256), 0, stream, ids, dy, v0, v_t, h, rows, dw);
+                     dim3(kEmbChunk / 2), 0, stream, ids, keys, v0, v_t, rows);
+  hipLaunchKernelGGL(embed_bwd_kernel<true>, grid, dim3(256), 0, stream, reinterpret_cast<const int64_t*>(keys), dy,
+                     v0, v_t, h, rows, dw);
   return hipGetLastError();
 }
 

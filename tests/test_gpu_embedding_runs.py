@@ -47,3 +47,31 @@ def test_gradient_matches_float64(n, h, ids):
     ref = torch.ones(v_t, h, device="cuda", dtype=torch.float64).index_add_(0, local[hit], full[hit])
     mag = torch.ones(v_t, h, device="cuda", dtype=torch.float64).index_add_(0, local[hit], full[hit].abs())
     assert bool(((dw.double() - ref).abs() <= n * 2.0 ** -24 * mag).all())
+
+
+def test_captured_backward_replays_on_kept_ids_and_full_arena_runs():
+    """A captured backward adds the same gradient on every replay (the stashed
+    ids stay as they are), and an arena that holds the ids alone still runs the
+    call, in token order.  Small whole numbers: every sum is exact in fp32."""
+    n, h, v = 4104, 256, 1000
+    rng = np.random.default_rng(3)
+    tok = torch.from_numpy(np.where(rng.random(n) < 0.3, 7, rng.integers(0, v, n)).astype(np.int64)).cuda()
+    model, par = L.make_model(h, h // 64, h // 64, 32, vocab=v), L.make_parallel(n)
+    dx = torch.randint(-4, 5, (1, n, h), device="cuda").to(torch.bfloat16)
+    table, x = torch.zeros(v, h, dtype=torch.bfloat16, device="cuda"), torch.empty(1, n, h, dtype=torch.bfloat16,
+                                                                                  device="cuda")
+    once = torch.zeros(v, h, device="cuda").index_add_(0, tok, dx[0].float())
+    for nbytes in (1 << 20, (8 * n + 255) // 256 * 256):
+        arena = L.Arena.on(torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+        dw = torch.zeros(v, h, device="cuda")
+        st = L.embedding_fwd(model, par, tok.view(1, n), table, x, arena)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            L.embedding_bwd(model, par, st, dx, dw, arena, stream=torch.cuda.current_stream())
+        assert arena.stats()["in_use"] == 0
+        for i in range(1, 4):
+            graph.replay()
+            torch.cuda.synchronize()
+            print(f"\n[embedding replay arena={nbytes} {i}]", flush=True)
+            assert torch.equal(dw, i * once)
