@@ -114,16 +114,18 @@ __device__ __forceinline__ int swz(int row) {
 // wait for their own copies (vmcnt) before the barrier that publishes a tile.
 // The LDS address is uniform by construction; readfirstlane states it for the
 // compiler, which otherwise may keep it in a vector register.
+// The s_nop is the wait state that gfx9 needs between a scalar write of m0 and a
+// copy into LDS that reads it; the compiler adds none inside an assembly block.
 __device__ __forceinline__ uint32_t lds_addr(const void* lds) {
   return __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(LPTR(const_cast<void*>(lds)))));
 }
 template <int IMM>
 __device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t lds) {   // LDS chunk at lds + IMM
-  asm volatile("s_add_u32 m0, %2, %3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds), "n"(IMM)
+  asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds), "n"(IMM)
                : "memory", "m0", "scc");
 }
 __device__ __forceinline__ void dma4(const void* sbase, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" ::"v"(voff), "s"(sbase), "s"(lds) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(voff), "s"(sbase), "s"(lds) : "memory", "m0");
 }
 
 // Copy rows [0, ROWS) of src (row stride ld, rows >= n_valid clamped to the

@@ -62,6 +62,9 @@ __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(ui
 // LDS read of the next stage, exposing the copy latency on every stage.  The
 // kernels wait for their own copies (vmcnt) before the barrier that publishes
 // a stage, and before the stages are reused as epilogue staging space.
+// A scalar write of m0 needs one wait state before a copy into LDS reads it
+// (gfx9), which the compiler adds around its own instructions but not inside an
+// assembly block: the s_nop is that wait.
 // TAG only changes the asm text (a comment), to keep copies in the two arms of
 // a branch from being merged.
 __device__ __forceinline__ uint32_t lds_addr(const uint8_t* lds) {
@@ -70,7 +73,7 @@ __device__ __forceinline__ uint32_t lds_addr(const uint8_t* lds) {
 }
 template <int TAG = 0>
 __device__ __forceinline__ void dma16(const uint16_t* g, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off ; copy form %2" ::"v"(g), "s"(lds), "n"(TAG)
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off ; copy form %2" ::"v"(g), "s"(lds), "n"(TAG)
                : "memory", "m0");
 }
 template <int TAG = 0>
