@@ -301,9 +301,9 @@ int lm_head_xent_noalloc(int64_t n_tokens, int64_t hidden, int64_t vocab_shard, 
  * output gradient (own rows dx: bf16 [b][s_sp][h]; peer rows peer_dx: bf16
  * [b][(t-1) s_sp][h], NULL iff t == 1) into d_w_emb: f32 [v_t][h], with fp32
  * atomic adds (tokens sharing an id add in no fixed order).  With more than 512
- * tokens it sorts them by id in 8 b s_c bytes of workspace from the arena; an
- * arena without room for them still runs the call, slower where ids repeat.  It
- * releases the stash.
+ * tokens and b s_c h / t >= 2^20 it sorts them by id in 8 b s_c bytes of workspace
+ * from the arena; an arena without room for them still runs the call, slower
+ * where ids repeat.  It releases the stash.
  *
  * LM-head block: xn = RMSNorm(x; w_norm) on the own rows, all-gathered,
  * logits = xn W_lm^T in FP32 over the vocabulary shard, cross-entropy with

@@ -1182,7 +1182,7 @@ extern "C" int embedding_bwd(const l4d_model* m, const l4d_parallel* p, l4d_stas
   // the sorted tokens; an arena without room for them still runs the call, unsorted
   Workspace ws;
   ws.A = A;
-  ws.size = align_up(embed_bwd_ws_bytes(x.b * x.s_c));
+  ws.size = align_up(embed_bwd_ws_bytes(x.b * x.s_c, (int32_t)x.h, (int32_t)x.t));
   ws.held = ws.size && arena_alloc(A, ws.size, &ws.off);
   uint64_t* keys = ws.held ? reinterpret_cast<uint64_t*>(A->base + ws.off) : nullptr;
   if ((rc = launch("embed_bwd", s, [&] {

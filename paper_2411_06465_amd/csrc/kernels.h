@@ -245,9 +245,10 @@ hipError_t embed_fwd(const int64_t* ids, const uint16_t* w, int64_t v0, int32_t 
                      int32_t s_c, int32_t s_sp, int32_t r, int32_t t, const uint16_t* receipt, uint16_t* own,
                      uint16_t* send, int64_t* kept, hipStream_t stream);
 // dw[ids[m] - v0] += dy.row(m) for the ids in range (fp32 atomics).  keys:
-// embed_bwd_ws_bytes(rows) bytes in which the tokens are sorted by id, or NULL =
-// added in token order (slower where ids repeat).
-uint64_t embed_bwd_ws_bytes(int64_t rows);
+// embed_bwd_ws_bytes bytes in which the tokens are sorted by id, or NULL =
+// added in token order (slower where many ids repeat).  0 bytes: too few elements
+// for a sort to pay.
+uint64_t embed_bwd_ws_bytes(int64_t rows, int32_t h, int32_t t);
 hipError_t embed_bwd(const int64_t* ids, uint64_t* keys, RowSrc dy, int64_t v0, int32_t v_t, int32_t h, int64_t rows,
                      float* dw, hipStream_t stream);
 

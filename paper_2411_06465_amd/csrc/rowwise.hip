@@ -819,8 +819,16 @@ hipError_t embed_fwd(const int64_t* ids, const uint16_t* w, int64_t v0, int32_t 
   return hipGetLastError();
 }
 
-// Few tokens share few ids, and the sort would cost a launch of its own.
-uint64_t embed_bwd_ws_bytes(int64_t rows) { return rows <= 512 ? 0 : static_cast<uint64_t>(rows) * 8; }
+// The sort costs a launch and a fixed 11 us or so (a chain of 66 exchange steps),
+// what it saves grows with the rows that are added: about rows / t of them hit
+// this rank's shard.  From 2^20 gradient elements on, the sorted form is never
+// behind one atomic row per token, whatever the ids (hidden 4096 on TP 4: 1024
+// tokens 32 us against 39 with uniform ids, 31 against 74 with heavy-tailed ones);
+// below, token order is the faster one (hidden 512, TP 1, 1024 tokens: 16 us, sorted
+// 28, one atomic row per token 22; heavy-tailed 16, 27, 48).
+uint64_t embed_bwd_ws_bytes(int64_t rows, int32_t h, int32_t t) {
+  return rows <= 512 || rows * h / t < (int64_t{1} << 20) ? 0 : static_cast<uint64_t>(rows) * 8;
+}
 
 hipError_t embed_bwd(const int64_t* ids, uint64_t* keys, RowSrc dy, int64_t v0, int32_t v_t, int32_t h, int64_t rows,
                      float* dw, hipStream_t stream) {

@@ -1,7 +1,8 @@
 """GPU parity of the embedding gradient where its sorted runs can go wrong:
-token counts around a sort chunk (2048) and the unsorted limit (512), hidden
-sizes that are no multiple of a column block (1024), one id on every token, no
-id in range, against a float64 sum.  fp32 sums of at most n terms of either
+token counts around a sort chunk (2048) and the unsorted limits (512 tokens, 2^20
+elements in the rank's share of the rows), hidden sizes that are no multiple of a
+column block (1024), one id on every token, no id in range, against a float64
+sum.  fp32 sums of at most n terms of either
 sign: within n * 2^-24 of the sum of magnitudes."""
 import numpy as np
 import pytest
@@ -13,7 +14,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n,h,ids", [(8, 256, "mixed"), (512, 256, "mixed"), (520, 1280, "mixed"), (2048, 256, "same"),
-                                     (2056, 256, "mixed"), (4104, 768, "same"), (2056, 256, "none")])
+                                     (2056, 256, "mixed"), (4104, 768, "same"), (2056, 256, "none"),
+                                     # enough elements for the sort: whole chunks, one past a chunk, three chunks
+                                     (2048, 2304, "same"), (2056, 2304, "mixed"), (4104, 1280, "mixed"),
+                                     (2056, 2304, "none")])
 def test_gradient_matches_float64(n, h, ids):
     print(f"\n[embedding runs n={n} h={h} {ids}]", flush=True)
     v, t, rank = 4000, 4, 1
@@ -75,3 +79,23 @@ def test_captured_backward_replays_on_kept_ids_and_full_arena_runs():
             torch.cuda.synchronize()
             print(f"\n[embedding replay arena={nbytes} {i}]", flush=True)
             assert torch.equal(dw, i * once)
+
+
+@pytest.mark.parametrize("n,h,t,sorts", [(512, 8192, 1, False), (1024, 512, 1, False), (4096, 512, 4, False),
+                                         (4096, 256, 1, True), (1024, 4096, 4, True), (520, 8192, 4, True)])
+def test_only_calls_with_enough_rows_sort(n, h, t, sorts):
+    """A call that adds fewer than 2^20 elements takes no workspace: its sort would take longer than its adds."""
+    print(f"\n[embedding sort rule n={n} h={h} tp={t}]", flush=True)
+    v = 1024
+    model, par = L.make_model(h, h // 64, h // 64, 32, vocab=v), L.make_parallel(n, tp=t)
+    arena = L.Arena.on(torch.empty(1 << 20, dtype=torch.uint8, device="cuda"))
+    ids = torch.arange(n, device="cuda").remainder_(v).view(1, n)
+    own, peer = (torch.ones(1, m, h, dtype=torch.bfloat16, device="cuda") for m in (n // t, n - n // t))
+    x, send = torch.empty_like(own), torch.empty_like(peer) if t > 1 else None
+    st = L.embedding_fwd(model, par, ids, torch.zeros(v // t, h, dtype=torch.bfloat16, device="cuda"), x, arena, send=send)
+    held = arena.stats()["peak"]
+    dw = torch.zeros(v // t, h, device="cuda")
+    L.embedding_bwd(model, par, st, own, dw, arena, peer_dx=peer if t > 1 else None)
+    torch.cuda.synchronize()
+    assert arena.stats()["peak"] - held == (8 * n + 255) // 256 * 256 * sorts
+    assert torch.equal(dw, torch.bincount(ids[0], minlength=v)[:v // t].float()[:, None].expand_as(dw))
