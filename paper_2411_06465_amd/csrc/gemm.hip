@@ -977,13 +977,34 @@ __device__ __forceinline__ uint32_t tile_lane_off(const Operand& op, int x0, int
   const int kr = RPI * wave + lane / LPR;
   return static_cast<uint32_t>(kr * op.src.ld + min(x0 + ((lane % LPR) ^ mn_swz<T>(kr)) * 8, op.rows - 8));
 }
+// First row of the stage at hand of a kRunRows operand: stages are taken in
+// order, so it moves 64 rows on within a slot, and a slot's first row is mapped
+// when the walk enters it.  Mapping every stage (scalar divisions, and the
+// kernel for any slots, whose lanes map their own rows) cost more than the products: M 768
+// N 4096 K 8192 on 128-row tiles 124 us, 94 now; M 1024 N 512 K 4096 on 64-row
+// ones 42 and 28 (36 and 23 where no rows are gathered).
+struct RunWalk {
+  const uint16_t* base = nullptr;
+  int left = 0;                // stages of the slot after the one at hand
+  __device__ __forceinline__ void next(const RowSrc& src, int k0, int K) {
+    if (--left >= 0) {
+      base += static_cast<int64_t>(BK2) * src.ld;
+      return;
+    }
+    k0 = min(k0, K - 1);       // stages past K copy zeros
+    base = mapped_row(src, k0);
+    left = (src.t == 1 ? K - k0 - 1 : src.s_sp - k0 % src.s_sp - 1) / BK2;
+  }
+};
 template <int T, int W, int MAP>
-__device__ __forceinline__ StageSrc<T / (8 * W)> tile_src_mn(const Operand& op, uint32_t off, int x0, int k0, int K,
-                                                             int wave, int lane) {
+__device__ __forceinline__ StageSrc<T / (8 * W)> tile_src_mn(const Operand& op, uint32_t off, RunWalk& run, int x0,
+                                                             int k0, int K, int wave, int lane) {
   constexpr int LPR = T / 8, RPI = 64 / LPR, C = T / (8 * W);
   StageSrc<C> r;
+  if constexpr (MAP == kRunRows) run.next(op.src, k0, K);
   if (MAP != kAnyRows || op.src.t == 1 || op.src.s_sp % BK2 == 0) {   // uniform: the stage is one run of rows (see copy2_mn)
-    const uint16_t* base0 = (MAP != kPlainRows ? mapped_row(op.src, min(k0, K - 1))
+    const uint16_t* base0 = (MAP == kRunRows   ? run.base
+                             : MAP == kAnyRows ? mapped_row(op.src, min(k0, K - 1))
                                                : op.src.own + static_cast<int64_t>(k0) * op.src.ld) + off;
 #pragma unroll
     for (int q = 0; q < C; ++q) {
@@ -1043,12 +1064,13 @@ __global__ void __launch_bounds__(W * 64) gemm_tile(GemmParams p) {
   else ob = tile_lane_off<T>(p.B, tn * T, wave, lane);
   const uint32_t ring_addr = lds_addr(ring) + wave * 1024;
   StageSrc<C> ga, gb;
+  RunWalk run_a, run_b;
   auto prepare = [&](int st) __attribute__((always_inline)) {
     const int k0 = (st0 + st) * BK2;
     if constexpr (LA == Layout::KC) ga = tile_src_kc<T, W>(ra, k0, p.K);
-    else ga = tile_src_mn<T, W, MAP>(p.A, oa, tm * T, k0, p.K, wave, lane);
+    else ga = tile_src_mn<T, W, MAP>(p.A, oa, run_a, tm * T, k0, p.K, wave, lane);
     if constexpr (LB == Layout::KC) gb = tile_src_kc<T, W>(rb, k0, p.K);
-    else gb = tile_src_mn<T, W, MAP>(p.B, ob, tn * T, k0, p.K, wave, lane);
+    else gb = tile_src_mn<T, W, MAP>(p.B, ob, run_b, tn * T, k0, p.K, wave, lane);
   };
   auto fire = [&](int c, int slot) __attribute__((always_inline)) {   // copy c of the prepared stage
     dma16(c < C ? ga.g[c % C] : gb.g[c % C], ring_addr + slot * STB + (c < C ? 0 : OPB) + c % C * (W * 1024));
@@ -1254,7 +1276,9 @@ hipError_t launch(const GemmParams& p, hipStream_t stream) {
   if constexpr (LA == Layout::MN) {            // the weight gradients: gathered activations as MN operands
     const bool runs = (a.t == 1 || a.s_sp % BK2 == 0) && (b.t == 1 || b.s_sp % BK2 == 0);
     if (small)
-      return plain ? launch_small<LA, LB, KIND, kPlainRows>(p, stream) : launch_small<LA, LB, KIND, kAnyRows>(p, stream);
+      return plain  ? launch_small<LA, LB, KIND, kPlainRows>(p, stream)
+             : runs ? launch_small<LA, LB, KIND, kRunRows>(p, stream)
+                    : launch_small<LA, LB, KIND, kAnyRows>(p, stream);
     return plain  ? launch256<LA, LB, KIND, PAIR, kPlainRows>(p, stream)
            : runs ? launch256<LA, LB, KIND, PAIR, kRunRows>(p, stream)
                   : launch256<LA, LB, KIND, PAIR, kAnyRows>(p, stream);

@@ -23,6 +23,12 @@ LAYERS = [
     W.LayerWorkload("tiles-tp2-s200", 512, 4, 2, 1376, 200, tp=2, tp_rank=0, n_gpus=2, rope_base=5e5),
     # 128-row tiles, one and two per CU, M = 1000 and FFN 2728 ragged; head size 64 in 128-column tiles
     W.LayerWorkload("tiles-128", 1024, 16, 4, 2728, 1000, rope_base=5e5),
+    # gathered slots of one, two and three 64-row stages in 64-row tiles, two sequences
+    W.LayerWorkload("tiles-tp2-s128", 256, 4, 2, 688, 128, micro_batch=2, tp=2, tp_rank=1, n_gpus=2),
+    W.LayerWorkload("tiles-tp4-s512", 512, 8, 4, 1376, 512, tp=4, tp_rank=2, n_gpus=4, rope_base=5e5),
+    W.LayerWorkload("tiles-tp2-s384", 512, 4, 2, 1376, 384, micro_batch=3, tp=2, tp_rank=0, n_gpus=2, rope_base=5e5),
+    # gathered slots of 64 rows in 128-row tiles
+    W.LayerWorkload("tiles-128-tp4", 4096, 32, 8, 2048, 256, tp=4, tp_rank=3, n_gpus=4, rope_base=5e5),
     # 256-row tiles over 200 tokens (K ragged) with gathered slots of 100 rows
     W.LayerWorkload("tiles-256-tp2", 4096, 32, 8, 6144, 200, tp=2, tp_rank=1, n_gpus=2, rope_base=5e5),
 ]
