@@ -509,7 +509,8 @@ struct FwdWs {
   uint64_t rope, o_send, ffn_send, total;
 };
 struct BwdWs {
-  uint64_t rope, dgu, dxn2, dh1, dh1_f32, dctx, delta, dqkv, dxn1, partial, dxn2_send, dxn1_send, dkv, dwpart, total;
+  uint64_t rope, dgu, dxn2, dh1, dh1_f32, dctx, delta, dqkv, dxn1, partial, dxn2_send, dxn1_send, dkv, ffn_part, proj_part,
+      total;
 };
 
 // fp32 partials of a GEMM cut into `splits` parts.
@@ -548,17 +549,25 @@ BwdWs plan_bwd(const Shard& x, const l4d_peer_outputs* sends) {
   w.dqkv = cv.take(tok * qkv_cols(x) * 2);
   w.dxn1 = cv.take(2 * sp);       // fp32
   w.partial = cv.take((uint64_t)rmsnorm_bwd_partials(x.b * x.s_sp) * x.h * 4);
+  const uint64_t partial_end = cv.used;
   w.dxn2_send = (x.t > 1 && !(sends && sends->dxn2_partial)) ? cv.take(peer_rows) : 0;
   w.dxn1_send = (x.t > 1 && !(sends && sends->dxn1_partial)) ? cv.take(peer_rows) : 0;
   // fp32 dK/dV partials when the query heads of a kv-head are split (at most a/k slices)
   const int64_t group = x.a / x.k;
   w.dkv = group > 1 ? cv.take(2 * (uint64_t)group * x.b * x.s * x.k_t * x.d * 4) : 0;
-  // fp32 partials of the weight-gradient GEMMs that split their K (token) range
+  // fp32 partials of the GEMMs that split their K range lie where nothing lives at
+  // that time: those of the FFN's weight gradients from dh1 to the norm partials, which
+  // are written after them, those of the two projections in dgu and dxn2, which are
+  // read before them.  Only what does not fit there takes room of its own.
   const int64_t tk = (int64_t)tok;
-  const uint64_t dwp = std::max({split_ws_bytes(x.h, x.f_t, tk), split_ws_bytes(2 * x.f_t, x.h, tk),
-                                 split_ws_bytes(x.h, x.a_t * x.d, tk), split_ws_bytes(qkv_cols(x), x.h, tk),
-                                 split_ws_bytes(tk, x.a_t * x.d, x.h, false)});   // and the O dX GEMM
-  w.dwpart = dwp ? cv.take(dwp) : 0;
+  const uint64_t ffn = std::max(split_ws_bytes(x.h, x.f_t, tk), split_ws_bytes(2 * x.f_t, x.h, tk));
+  const uint64_t proj = std::max({split_ws_bytes(x.h, x.a_t * x.d, tk), split_ws_bytes(qkv_cols(x), x.h, tk),
+                                  split_ws_bytes(tk, x.a_t * x.d, x.h, false)});   // and the O dX GEMM
+  const bool ffn_in = ffn <= partial_end - w.dh1, proj_in = proj <= w.dh1 - w.dgu;
+  const uint64_t own = std::max(ffn_in ? 0 : ffn, proj_in ? 0 : proj);
+  const uint64_t own_off = own ? cv.take(own) : 0;
+  w.ffn_part = ffn_in ? w.dh1 : own_off;
+  w.proj_part = proj_in ? w.dgu : own_off;
   w.total = cv.used;
   return w;
 }
@@ -903,7 +912,7 @@ extern "C" int llama_layer_bwd(const l4d_model* m, const l4d_parallel* p, const 
   float *dxn2 = F(plan.dxn2), *dxn1 = F(plan.dxn1), *dh1_f32 = F(plan.dh1_f32);
   float* delta = reinterpret_cast<float*>(wsb + plan.delta);
   float* partial = reinterpret_cast<float*>(wsb + plan.partial);
-  float* dwpart = plan.dwpart ? reinterpret_cast<float*>(wsb + plan.dwpart) : nullptr;
+  float *ffn_part = F(plan.ffn_part), *proj_part = F(plan.proj_part);
   const l4d_peer_inputs none{};
   const l4d_peer_inputs& pi = peers ? *peers : none;
   void* dxn2_send = (sends && sends->dxn2_partial) ? sends->dxn2_partial : (void*)W(plan.dxn2_send);
@@ -928,7 +937,7 @@ extern "C" int llama_layer_bwd(const l4d_model* m, const l4d_parallel* p, const 
       return r;
     // dW_down += dy_full^T prod
     if ((r = run_gemm("gemm_down_dw", s, x.h, x.f_t, tok, op(dy_full, x.h), Layout::MN,
-                      op(RowSrc::plain(sptr(st, L4D_STASH_PROD), x.f_t), x.f_t), Layout::MN, epi_acc(dw->down, x.f_t), dwpart)))
+                      op(RowSrc::plain(sptr(st, L4D_STASH_PROD), x.f_t), x.f_t), Layout::MN, epi_acc(dw->down, x.f_t), ffn_part)))
       return r;
     // d(xn2) = dGU W_gu (own rows + receipt; peers' rows sent)
     if ((r = run_gemm("gemm_gate_up_dx", s, tok, x.h, 2 * x.f_t, op(RowSrc::plain(dgu, 2 * x.f_t), tok), Layout::KC,
@@ -937,7 +946,7 @@ extern "C" int llama_layer_bwd(const l4d_model* m, const l4d_parallel* p, const 
       return r;
     const RowSrc xn2_full = gathered(sptr(st, L4D_STASH_XN2), pi.sp_peer_xn2, x);
     if ((r = run_gemm("gemm_gate_up_dw", s, 2 * x.f_t, x.h, tok, op(RowSrc::plain(dgu, 2 * x.f_t), 2 * x.f_t),
-                      Layout::MN, op(xn2_full, x.h), Layout::MN, epi_acc(dw->gate_up, x.h), dwpart)))
+                      Layout::MN, op(xn2_full, x.h), Layout::MN, epi_acc(dw->gate_up, x.h), ffn_part)))
       return r;
     // norm-2 backward + residual: dh1 in bf16 (product operand) and fp32 (residual of dx)
     if ((r = launch("rmsnorm2_bwd", s, [&] {
@@ -952,10 +961,10 @@ extern "C" int llama_layer_bwd(const l4d_model* m, const l4d_parallel* p, const 
     // attention output projection
     const RowSrc dh1_full = gathered(dh1, pi.sp_peer_dh1, x);
     if ((r = run_gemm("gemm_o_dx", s, tok, nq, x.h, op(dh1_full, tok), Layout::KC, op(RowSrc::plain(w->o, nq), nq),
-                      Layout::MN, epi_store(dctx, nq), dwpart)))
+                      Layout::MN, epi_store(dctx, nq), proj_part)))
       return r;
     if ((r = run_gemm("gemm_o_dw", s, x.h, nq, tok, op(dh1_full, x.h), Layout::MN,
-                      op(RowSrc::plain(sptr(st, L4D_STASH_CTX), nq), nq), Layout::MN, epi_acc(dw->o, nq), dwpart)))
+                      op(RowSrc::plain(sptr(st, L4D_STASH_CTX), nq), nq), Layout::MN, epi_acc(dw->o, nq), proj_part)))
       return r;
     // attention backward -> dQKV (inverse RoPE applied), remote dK/dV
     AttnParams ap = attn_params(x);
@@ -992,7 +1001,7 @@ extern "C" int llama_layer_bwd(const l4d_model* m, const l4d_parallel* p, const 
       return r;
     const RowSrc xn1_full = gathered(sptr(st, L4D_STASH_XN1), pi.sp_peer_xn1, x);
     if ((r = run_gemm("gemm_qkv_dw", s, qc, x.h, tok, op(RowSrc::plain(dqkv, qc), qc), Layout::MN, op(xn1_full, x.h),
-                      Layout::MN, epi_acc(dw->qkv, x.h), dwpart)))
+                      Layout::MN, epi_acc(dw->qkv, x.h), proj_part)))
       return r;
     // norm-1 backward + residual
     if ((r = launch("rmsnorm1_bwd", s, [&] {

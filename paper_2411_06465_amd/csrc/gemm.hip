@@ -190,7 +190,7 @@ __device__ __forceinline__ int64_t resid_row(const EpiParams& e, int64_t m, bool
 }
 
 // The two halves start at columns n_lo and n_lo + pair.
-template <EpiKind KIND>
+template <EpiKind KIND, bool STREAM = false>
 __device__ __forceinline__ void epi_load(const GemmParams& p, int64_t m, int n_lo, int pair, EpiIn<KIND>& in) {
   const EpiParams& e = p.epi;
   if (m >= p.M) return;
@@ -222,8 +222,13 @@ __device__ __forceinline__ void epi_load(const GemmParams& p, int64_t m, int n_l
       const int n = n_lo + h * pair;
       if (n >= p.N) continue;
       const f32x4_a4* c = reinterpret_cast<const f32x4_a4*>(static_cast<const float*>(e.c) + m * e.ldc + n);
-      in.c[2 * h] = c[0];
-      in.c[2 * h + 1] = c[1];
+      if constexpr (STREAM) {
+        in.c[2 * h] = __builtin_nontemporal_load(c);
+        in.c[2 * h + 1] = __builtin_nontemporal_load(c + 1);
+      } else {
+        in.c[2 * h] = c[0];
+        in.c[2 * h + 1] = c[1];
+      }
     }
   } else if constexpr (KIND == EpiKind::QkvRope) {
     if (n_lo >= p.N || n_lo >= e.nq + e.nk) return;     // V columns are not rotated
@@ -236,7 +241,7 @@ __device__ __forceinline__ void epi_load(const GemmParams& p, int64_t m, int n_l
 }
 
 // lo: 8 columns starting at column n_lo; hi: the 8 columns `pair` further.
-template <EpiKind KIND>
+template <EpiKind KIND, bool STREAM = false>
 __device__ __forceinline__ void epilogue(const GemmParams& p, int64_t m, int n_lo, int pair, float* lo, float* hi,
                                          const EpiIn<KIND>& in) {
   const EpiParams& e = p.epi;
@@ -269,8 +274,12 @@ __device__ __forceinline__ void epilogue(const GemmParams& p, int64_t m, int n_l
           const float* src = h ? hi : lo;
           float* c = static_cast<float*>(e.c) + m * e.ldc + n;
 #pragma unroll
-          for (int q = 0; q < 2; ++q)
-            *reinterpret_cast<f32x4_a4*>(c + 4 * q) = in.c[2 * h + q] + f32x4{src[4 * q], src[4 * q + 1], src[4 * q + 2], src[4 * q + 3]};
+          for (int q = 0; q < 2; ++q) {
+            const f32x4 v = in.c[2 * h + q] + f32x4{src[4 * q], src[4 * q + 1], src[4 * q + 2], src[4 * q + 3]};
+            f32x4_a4* out = reinterpret_cast<f32x4_a4*>(c + 4 * q);
+            if constexpr (STREAM) __builtin_nontemporal_store(static_cast<f32x4_a4>(v), out);
+            else *out = v;
+          }
         }
       }
       break;
@@ -979,10 +988,10 @@ __device__ __forceinline__ uint32_t tile_lane_off(const Operand& op, int x0, int
 }
 // First row of the stage at hand of a kRunRows operand: stages are taken in
 // order, so it moves 64 rows on within a slot, and a slot's first row is mapped
-// when the walk enters it.  Mapping every stage (scalar divisions, and the
-// kernel for any slots, whose lanes map their own rows) cost more than the products: M 768
-// N 4096 K 8192 on 128-row tiles 124 us, 94 now; M 1024 N 512 K 4096 on 64-row
-// ones 42 and 28 (36 and 23 where no rows are gathered).
+// when the walk enters it.  The form for any slots, whose lanes map their own
+// rows on every stage, spends more on that than on the products: M 768 N 4096 K
+// 8192 on 128-row tiles 124 us, this walk 94; M 1024 N 512 K 4096 on 64-row tiles
+// 42 and 28 (23 where no rows are gathered).
 struct RunWalk {
   const uint16_t* base = nullptr;
   int left = 0;                // stages of the slot after the one at hand
@@ -1029,7 +1038,7 @@ __device__ __forceinline__ void wait_copies() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-template <Layout LA, Layout LB, EpiKind KIND, int T, int W, int S, int MAP>
+template <Layout LA, Layout LB, EpiKind KIND, int T, int W, int S, int MAP, bool STREAM>
 __global__ void __launch_bounds__(W * 64) gemm_tile(GemmParams p) {
   constexpr int OPB = T * BK2 * 2, STB = 2 * OPB;   // bytes per operand and per stage
   constexpr int R = T / 64;                         // 32-row blocks per wave and operand
@@ -1177,7 +1186,7 @@ __global__ void __launch_bounds__(W * 64) gemm_tile(GemmParams p) {
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) {
       const int idx = it * (W * 64) + tid;
-      epi_load<KIND>(p, tm * T + idx / VPR, column(idx % VPR), pair, in[it]);
+      epi_load<KIND, STREAM>(p, tm * T + idx / VPR, column(idx % VPR), pair, in[it]);
     }
   }
   __syncthreads();    // every wave is done reading the ring
@@ -1228,15 +1237,25 @@ __global__ void __launch_bounds__(W * 64) gemm_tile(GemmParams p) {
     }
     float lo[8] = {l0.x, l0.y, l0.z, l0.w, l1.x, l1.y, l1.z, l1.w};
     float hi[8] = {h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w};
-    epilogue<KIND>(p, m, column(v), pair, lo, hi, in[it]);
+    epilogue<KIND, STREAM>(p, m, column(v), pair, lo, hi, in[it]);
   }
 }
+
+// A weight gradient of this size is streamed past the caches, as the 256-row
+// kernel does with all of them: left there it displaces the operands of the
+// kernels that follow (a layer of hidden 2048, FFN 5464 on 1000 tokens 677 us, streamed
+// 630; hidden 4096, FFN 11008 on TP 4, 1024 tokens 637 and 602), while smaller ones
+// are found there by the next call (hidden 1024 on 1000 tokens 302, streamed 307).
+constexpr int64_t kStreamBytes = 32 << 20;
 
 template <Layout LA, Layout LB, EpiKind KIND, int T, int W, int S, int MAP>
 hipError_t launch_tile(const GemmParams& p, hipStream_t stream) {
   const int parts = p.k_splits > 1 ? p.k_splits : 1;
-  const unsigned tiles = static_cast<unsigned>((p.M + T - 1) / T) * ((p.N + T - 1) / T);
-  hipLaunchKernelGGL((gemm_tile<LA, LB, KIND, T, W, S, MAP>), dim3(tiles * parts), dim3(W * 64), 0, stream, p);
+  const dim3 grid(static_cast<unsigned>((p.M + T - 1) / T) * ((p.N + T - 1) / T) * parts);
+  if (KIND == EpiKind::AccF32 && static_cast<int64_t>(p.M) * p.N * 4 >= kStreamBytes)
+    hipLaunchKernelGGL((gemm_tile<LA, LB, KIND, T, W, S, MAP, KIND == EpiKind::AccF32>), grid, dim3(W * 64), 0, stream, p);
+  else
+    hipLaunchKernelGGL((gemm_tile<LA, LB, KIND, T, W, S, MAP, false>), grid, dim3(W * 64), 0, stream, p);
   return hipGetLastError();
 }
 
@@ -1394,49 +1413,84 @@ int gemm_max_splits(int64_t M, int64_t N, int64_t K, bool acc_f32) {
 }
 
 namespace {
-// Microseconds of a grid of T-row tiles, `st` stages of 64 k each, on a kernel
-// that keeps `slots` workgroups on the chip: per round of workgroups a fixed
-// part (launch or drain, first copies), the tile's share of C traffic at 4.8
-// TB/s and c0 + c1 fill per stage, where fill is the part of the slots in use
-// (an emptier chip clocks higher and waits less for memory).
-double grid_us(int64_t tiles, int64_t st, int T, int slots, double fixed, double c0, double c1) {
-  const double c_us = static_cast<double>(slots) * T * T * 8.0 / 4.8e6;
-  const auto round = [&](double fill) { return fixed + fill * c_us + st * (c0 + c1 * fill); };
-  const int64_t full = tiles / slots, rest = tiles % slots;
-  return full * round(1.0) + (rest ? round(static_cast<double>(rest) / slots) : 0.0);
+// What a grid of T-row tiles costs on a kernel that keeps `slots` workgroups on
+// the chip: per round of workgroups a fixed part (launch or drain, first copies),
+// the tiles' C traffic at c_tbs TB/s and c0 + c1 fill us per stage of 64 k, where fill is
+// the part of the slots in use (an emptier chip clocks higher and waits less for
+// memory); m_edge and n_edge once per grid whose last tiles are cut in M, in N.
+struct GridCost {
+  int T, slots;
+  double fixed, c_tbs, c0, c1, m_edge = 0.0, n_edge = 0.0;
+};
+double grid_us(const GridCost& g, int64_t tiles, int64_t st, double c_bytes) {
+  const double c_us = static_cast<double>(g.slots) * g.T * g.T * c_bytes / (g.c_tbs * 1e6);
+  const auto round = [&](double fill) { return g.fixed + fill * c_us + st * (g.c0 + g.c1 * fill); };
+  const int64_t full = tiles / g.slots, rest = tiles % g.slots;
+  return full * round(1.0) + (rest ? round(static_cast<double>(rest) / g.slots) : 0.0);
 }
+// 256-row tiles, 128 one and two workgroups per CU, 64 one and two per CU.
+//
+// Forward and dX (a K-contiguous operand): fits to GEMMs of 128 to 8192 rows, 256
+// to 32064 columns and K 128 to 32000 timed in every form on one MI355X, within
+// about 15% of the times, the traffic of C at 8 bytes an element: e.g. M 2048 N
+// 2048 K 5464 K-contiguous 125 us with 64 tiles of 256 rows, 60 with 256 of 128; M
+// 600 N 1280 K 8192 143 / 52 / 27 us with tiles of 256 / 128 / 64; M 4000 N 7168
+// K 4096 210 / 249 / 402; M 512 N 4096 K 32000 605 in one part and 317 in two with
+// 256-row tiles, 274 and 161 with 128-row ones.
+constexpr GridCost kForward[5] = {{256, 256, 8.0, 4.8, 1.0, 0.65},
+                                  {128, 256, 5.0, 4.8, 0.33, 0.27},
+                                  {128, 512, 5.0, 4.8, 0.25, 0.85},
+                                  {64, 256, 4.0, 4.8, 0.15, 0.06},
+                                  {64, 512, 4.0, 4.8, 0.20, 0.32}};
+// Weight gradients (both operands transposed, C read and written): fits to 393
+// of them, hidden 256 to 8192 and K 512 to 16384, each timed in 9 forms (rms error
+// 7 to 16% over the forms within 1.6 times the best).  The form picked takes 0.5% more
+// than the best one on average (at worst 27%: M 2752 N 4096 K 512, 46 us against
+// 36); with the constants above it took 2.7%, at worst 57% (M 4096 N 2752 K 1024: 82
+// us on 256-row tiles, whose cut tiles add C element by element, 52 on 128-row
+// ones; M 1024 N 1024 K 16384: 87 us unsplit on 64-row tiles, 59 in 4 parts on
+// 128-row ones).
+constexpr GridCost kWeightGrad[5] = {{256, 256, 12.6, 8.9, 1.20, 0.40, 7.0, 23.0},
+                                     {128, 256, 9.8, 7.0, 0.43, 0.18},
+                                     {128, 512, 11.6, 28.0, 0.73, 0.35},
+                                     {64, 256, 8.3, 1e3, 0.24, 0.06},
+                                     {64, 512, 5.9, 1e3, 0.34, 0.14}};
 }  // namespace
 
-// The constants of grid_us are fits to GEMMs of 128 to 8192 rows, 256 to 32064
-// columns and K 128 to 32000 timed in every form on one MI355X (per 64-k stage:
-// 256-row tiles 1.0 us nearly alone, 1.65-1.8 on a full chip; 128-row tiles one
-// per CU 0.37 / 0.6, two per CU 1.1 for both; 64-row tiles one per CU 0.17 /
-// 0.2, two 0.52), within about 15% of the times: e.g. M 2048 N 2048 K 5464
-// K-contiguous 125 us with 64 tiles of 256 rows, 60 with 256 of 128; M 600 N
-// 1280 K 8192 143 / 52 / 27 us with tiles of 256 / 128 / 64; M 4000 N 7168 K
-// 4096 210 / 249 / 402; M 512 N 4096 K 32000 605 in one part and 317 in two
-// with 256-row tiles, 274 and 161 with 128-row ones.
 GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, EpiKind kind, int max_splits) {
   const bool acc = kind == EpiKind::AccF32;
+  const GridCost* cost = acc ? kWeightGrad : kForward;
   const int64_t stages = (K + BK2 - 1) / BK2;
-  const auto tiles = [&](int64_t T) { return (M + T - 1) / T * ((N + T - 1) / T); };
+  const double mn = static_cast<double>(M) * N;
   GemmPlan best{256, 1};
   double best_us = 1e30;
   for (int s = 1; s <= max_splits; ++s) {
     if (s > 1 && (N % 4 != 0 || stages < 4 * s)) break;
     const int n_part = s == 1 ? 0 : (acc ? s - 1 : s);
-    const double reduce = s == 1 ? 0.0 : 4.0 + n_part * 8.0 * static_cast<double>(M) * N / 4e6;
     const int64_t st = (stages + s - 1) / s;
-    const auto offer = [&](int T, double us) {
-      if (us + reduce < 0.97 * best_us) {
-        best = GemmPlan{T, s};
-        best_us = us + reduce;
+    for (int f = 0; f < 5; ++f) {
+      const GridCost& g = cost[f];
+      const int64_t tiles = (M + g.T - 1) / g.T * ((N + g.T - 1) / g.T) * s;
+      if (g.T == 256 && s > 1 && K % (2 * BK2 * s) != 0) continue;     // that kernel takes equal, even parts
+      if (g.T != 256 && (tiles <= 256) != (g.slots == 256)) continue;  // see launch_small
+      // Parts store 4 bytes an element, but for part 0 of an accumulate, which reads
+      // and writes C.  The reduce pass reads the partials and writes C (an
+      // accumulate reads it too), 5.7 us and 6.9 TB/s over 5 to 55 us.  The price of
+      // dX parts on small tiles stands for their stores as well.
+      double c_bytes = 8.0, reduce = 0.0;
+      if (s > 1) {
+        reduce = 5.7 + (4.0 * n_part + (acc ? 8.0 : 2.0)) * mn / 6.9e6;
+        if (acc) c_bytes = (8.0 + 4.0 * n_part) / s;
+        else if (g.T == 256) c_bytes = 4.0;
+        else reduce = 4.0 + n_part * 8.0 * mn / 4e6;
       }
-    };
-    if (s == 1 || K % (2 * BK2 * s) == 0) offer(256, grid_us(tiles(256) * s, (st + 1) / 2 * 2, 256, 256, 8.0, 1.0, 0.65));
-    const int64_t t128 = tiles(128) * s, t64 = tiles(64) * s;
-    offer(128, t128 <= 256 ? grid_us(t128, st, 128, 256, 5.0, 0.33, 0.27) : grid_us(t128, st, 128, 512, 5.0, 0.25, 0.85));
-    offer(64, t64 <= 256 ? grid_us(t64, st, 64, 256, 4.0, 0.15, 0.06) : grid_us(t64, st, 64, 512, 4.0, 0.20, 0.32));
+      const double us = reduce + grid_us(g, tiles, g.T == 256 ? (st + 1) / 2 * 2 : st, c_bytes) +
+                        (M % g.T ? g.m_edge : 0.0) + (N % g.T ? g.n_edge : 0.0);
+      if (us < 0.97 * best_us) {       // a split or a smaller tile has to win by a margin
+        best = GemmPlan{g.T, s};
+        best_us = us;
+      }
+    }
   }
   return best;
 }

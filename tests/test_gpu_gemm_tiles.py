@@ -1,14 +1,15 @@
 """GPU parity of the GEMM forms at the sizes where they can go wrong, through
 the layer and the LM head: tiles of 64, 128 and 256 rows with ragged edges in
 M, N and K, token counts that are no multiple of 8 (the reduction length of the
-weight gradients), gathered operands whose slots are no multiple of 64 rows,
-split K ranges, and float-aligned gradient accumulators.  Bar: gpu_common's."""
+weight gradients), gathered operands whose slots are and are no multiple of 64
+rows, split K ranges, and float-aligned gradient accumulators.  Bar: gpu_common's."""
 import pytest
 import torch
 
 import workloads as W
 from oracle import lm_head as OLM
 from oracle.bf16 import from_bits
+from gemm_plans import layer_plans
 from gpu_common import Buffers, check, compare_layer, host_f64, oracle_layer
 from test_gpu_lm_head import run_lm
 
@@ -42,6 +43,29 @@ def test_layer_matches_oracle(w):
     fw, bw = oracle_layer(w, buf.wbits, buf.abits)
     ok, rep = compare_layer(w, buf, saved, fw, bw)
     assert ok, "\n".join(rep)
+
+
+# Layers whose backward cuts K ranges in parts, with the products that do, as
+# (rows of a tile, parts): every tile size, plain and gathered rows (slots of 512,
+# parts that start inside one), and a bf16 store.  Eight short sequences, so that
+# the oracle's attention stays small.
+SPLITS = [
+    (W.LayerWorkload("split-64-128", 256, 4, 2, 1376, 1024, micro_batch=8, rope_base=5e5),
+     dict(o_dw=(64, 4), qkv_dw=(64, 4), down_dw=(64, 4), gate_up_dw=(128, 4))),
+    (W.LayerWorkload("split-128-tp2", 1024, 8, 2, 64, 1024, micro_batch=8, tp=2, tp_rank=1, n_gpus=2, rope_base=5e5),
+     dict(qkv_dw=(128, 4), down_dw=(64, 4))),
+    (W.LayerWorkload("split-256-tp2", 2048, 16, 4, 64, 1024, micro_batch=8, tp=2, tp_rank=0, n_gpus=2, rope_base=5e5),
+     dict(qkv_dw=(256, 4), o_dw=(128, 4))),
+    (W.LayerWorkload("split-dx-tp4", 4096, 32, 8, 512, 128, tp=4, tp_rank=2, n_gpus=4, rope_base=5e5),
+     dict(o_dx=(64, 4))),
+]
+
+
+@pytest.mark.parametrize("w,splits", SPLITS, ids=lambda v: getattr(v, "name", ""))
+def test_layer_with_split_products_matches_oracle(w, splits):
+    plans = layer_plans(w)
+    assert {n: plans[n] for n in splits} == splits, plans      # else the case no longer tests what it is here for
+    test_layer_matches_oracle(w)
 
 
 # (tokens, hidden, vocabulary): a token count of 5 mod 8, where a row counted
