@@ -1338,7 +1338,7 @@ hipError_t gemm(const GemmParams& params, Layout la, Layout lb, hipStream_t stre
 
 namespace {
 // C += partial[0] + partial[1] + ..., four floats per thread (N % 4 == 0 and
-// ldc % 4 == 0 are required by the caller).
+// ldc % 4 == 0 are required by the caller; C may start at any float).
 __global__ void __launch_bounds__(256) split_reduce_kernel(float* __restrict__ c, int64_t ldc,
                                                           const float* __restrict__ part, int64_t M, int64_t N,
                                                           int32_t n_part) {
@@ -1346,15 +1346,9 @@ __global__ void __launch_bounds__(256) split_reduce_kernel(float* __restrict__ c
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   if (i >= M * n4) return;
   const int64_t m = i / n4, j = (i - m * n4) * 4;
-  float4* cp = reinterpret_cast<float4*>(c + m * ldc + j);
-  float4 v = *cp;
-  for (int s = 0; s < n_part; ++s) {
-    const float4 q = *reinterpret_cast<const float4*>(part + static_cast<int64_t>(s) * M * N + m * N + j);
-    v.x += q.x;
-    v.y += q.y;
-    v.z += q.z;
-    v.w += q.w;
-  }
+  f32x4_a4* cp = reinterpret_cast<f32x4_a4*>(c + m * ldc + j);
+  f32x4 v = *cp;
+  for (int s = 0; s < n_part; ++s) v += *reinterpret_cast<const f32x4*>(part + static_cast<int64_t>(s) * M * N + m * N + j);
   *cp = v;
 }
 // C (bf16) = partial[0] + partial[1] + ..., four columns per thread.

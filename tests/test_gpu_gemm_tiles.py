@@ -85,9 +85,8 @@ def test_lm_head_matches_oracle(n, h, v):
     assert ok, "\n".join(rep)
 
 
-def test_float_aligned_gradient_accumulators():
+def test_float_aligned_gradient_accumulators(w=W.TINY):
     # the accumulators may start at any float: the same bits as 16-byte aligned ones
-    w = W.TINY
     print("\n[float-aligned accumulators]", flush=True)
     buf = Buffers(w)
     buf.run(keep_stash=False)
@@ -96,3 +95,10 @@ def test_float_aligned_gradient_accumulators():
     buf.run(keep_stash=False)
     for k, v in want.items():
         assert torch.equal(buf.grads[k], v), k
+
+
+def test_float_aligned_accumulators_of_split_gradients():
+    # the pass that adds the parts reads and writes the accumulator too
+    w = SPLITS[0][0]
+    assert min(layer_plans(w)[n][1] for n in ("o_dw", "qkv_dw", "down_dw", "gate_up_dw")) > 1
+    test_float_aligned_gradient_accumulators(w)
