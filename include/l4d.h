@@ -154,11 +154,12 @@ int l4d_stash_release(l4d_arena* arena, l4d_stash* stash);
  * on top of the stash (so that callers can size an arena). */
 int l4d_layer_workspace_bytes(const l4d_model* model, const l4d_parallel* par,
                               uint64_t* fwd_bytes, uint64_t* bwd_bytes);
-/* Workspace lm_head_xent takes from the arena: the bf16 logits, plus an fp32
- * n_tokens x hidden buffer when vocab_shard is at least 1024 and not a multiple
- * of 128, plus, for few tokens, room for the fp32 partial sums of d_hidden over
- * parts of a long vocabulary shard.  With an arena that lacks only the last, the
- * call runs unsplit (slower, and d_hidden summed in another order). */
+/* Arena room for lm_head_xent: the bf16 logits, plus, for few tokens, the fp32
+ * partial sums of d_hidden over parts of a long vocabulary shard, and at least
+ * the logits plus n_tokens x hidden floats when vocab_shard is at least 1024
+ * and not a multiple of 128.  The call takes the logits and the partial sums;
+ * with an arena that lacks room for the latter it runs unsplit (slower, and
+ * d_hidden summed in another order). */
 int l4d_lm_head_workspace_bytes(int64_t n_tokens, int64_t hidden, int64_t vocab_shard,
                                 uint64_t* bytes);
 
@@ -267,11 +268,10 @@ int lm_head_xent(int64_t n_tokens, int64_t hidden, int64_t vocab_shard, int64_t 
 /* lm_head_xent without an arena, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc).  Same arguments, layouts, results and errors as
- * lm_head_xent, minus the arena: the logits (and, for a vocabulary shard with
- * a ragged tail, the fp32 sum of d_hidden) live in a 64 MiB array of device
+ * lm_head_xent, minus the arena: the logits live in a 64 MiB array of device
  * memory that the library holds per GPU, i.e. n_tokens * vocab_shard * 2
- * bytes, rounded up to 256, plus n_tokens * hidden * 4 for a shard of at least
- * 1024 that is not a multiple of 128, must fit in 67,108,864 bytes (e.g. 1024 tokens of a 32000-wide shard);
+ * bytes must fit in 67,108,864 bytes (e.g. 1024 tokens of a 32000-wide shard),
+ * and partial sums of d_hidden in what they leave of it;
  * larger problems return L4D_EINVAL before anything is launched.  The call
  * itself allocates nothing (the first call on a device looks up that
  * device's array once).  Every call on one GPU uses the same array: calls

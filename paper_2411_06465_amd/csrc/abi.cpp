@@ -595,14 +595,13 @@ extern "C" int l4d_layer_workspace_bytes(const l4d_model* m, const l4d_parallel*
 namespace {
 constexpr uint64_t kScratchBytes = 64ull << 20;   // lm_head_xent_noalloc's static workspace
 
-// Workspace of lm_head_xent.  `least` bytes are always enough: the bf16 logits,
-// plus n x h floats when the vocabulary shard is long and not a multiple of
-// 128.  `full` adds the fp32 partials of d_hidden, whose K range (the vocabulary
-// shard) is cut into `splits` parts where few token rows give few tiles.  The
-// split depends on the sizes alone -- where the logits fit the static workspace,
-// on what is left of it -- so that both entry points sum in the same order.
+// Workspace of lm_head_xent: the bf16 logits, and where few token rows give few
+// tiles the fp32 partials of d_hidden, whose K range (the vocabulary shard) is cut
+// into `splits` parts (`full` bytes; the logits alone run it unsplit).  The split
+// depends on the sizes alone -- where the logits fit the static workspace, on
+// what is left of it -- so that both entry points sum in the same order.
 struct LmWs {
-  uint64_t logits, least, full;
+  uint64_t logits, full;
   int splits;
 };
 LmWs plan_lm(int64_t n, int64_t h, int64_t v_t) {
@@ -610,17 +609,19 @@ LmWs plan_lm(int64_t n, int64_t h, int64_t v_t) {
   LmWs w;
   const uint64_t part = std::max<uint64_t>((uint64_t)n * h * 4, 1);
   w.logits = align_up((uint64_t)n * v_t * 2);
-  w.least = w.logits + (v_t % 128 != 0 && v_t >= 1024 ? align_up((uint64_t)n * h * 4) : 0);
   const uint64_t cap = w.logits <= kScratchBytes ? std::min(kMaxSplits, (kScratchBytes - w.logits) / part) : kMaxSplits;
   w.splits = n > 0 ? gemm_plan(n, h, v_t, EpiKind::StoreBF16, (int)std::max<uint64_t>(cap, 1)).splits : 1;
-  w.full = std::max(w.least, align_up(w.logits + partial_bytes(n, h, w.splits, false)));
+  w.full = align_up(w.logits + partial_bytes(n, h, w.splits, false));
   return w;
 }
 }  // namespace
 
 extern "C" int l4d_lm_head_workspace_bytes(int64_t n, int64_t h, int64_t v_t, uint64_t* bytes) {
   if (n < 0 || h <= 0 || v_t <= 0) return fail(L4D_EINVAL, "bad LM-head sizes");
-  if (bytes) *bytes = plan_lm(n, h, v_t).full;
+  // a long ragged shard is still quoted with n x h floats, as when d_hidden was summed there
+  const LmWs w = plan_lm(n, h, v_t);
+  const uint64_t quoted = w.logits + (v_t % 128 != 0 && v_t >= 1024 ? align_up((uint64_t)n * h * 4) : 0);
+  if (bytes) *bytes = std::max(w.full, quoted);
   return L4D_OK;
 }
 
@@ -1035,7 +1036,7 @@ int lm_xent_check(int64_t n, int64_t h, int64_t v_t, int64_t v0, const void* hid
   return L4D_OK;
 }
 
-// The LM-head kernel sequence over `bytes` >= plan_lm(n, h, v_t).least bytes of
+// The LM-head kernel sequence over `bytes` >= plan_lm(n, h, v_t).logits bytes of
 // device workspace at ws (256-byte aligned; nothing in it needs to start at
 // zero: every byte is written before it is read).
 int lm_xent_run(int64_t n, int64_t h, int64_t v_t, int64_t v0, const void* hidden, const void* w_lm,
@@ -1098,7 +1099,7 @@ extern "C" int lm_head_xent(int64_t n, int64_t h, int64_t v_t, int64_t v0, const
   ws.A = A;
   ws.size = plan.full;
   ws.held = arena_alloc(A, ws.size, &ws.off);
-  if (!ws.held && (rc = take_ws(A, plan.least, ws))) return rc;
+  if (!ws.held && (rc = take_ws(A, plan.logits, ws))) return rc;
   return lm_xent_run(n, h, v_t, v0, hidden, w_lm, targets, peer_lse, peer_z, grad_scale, loss, d_hidden, d_w,
                      reinterpret_cast<uint8_t*>(A->base + ws.off), ws.size, static_cast<hipStream_t>(stream_ptr));
 }
@@ -1109,7 +1110,7 @@ extern "C" int lm_head_xent_noalloc(int64_t n, int64_t h, int64_t v_t, int64_t v
                                     void* stream_ptr) {
   int rc = lm_xent_check(n, h, v_t, v0, hidden, w_lm, targets, peer_lse, peer_z, loss, d_hidden, d_w);
   if (rc) return rc;
-  const uint64_t need = plan_lm(n, h, v_t).least;
+  const uint64_t need = plan_lm(n, h, v_t).logits;
   if (need > kScratchBytes)
     return fail(L4D_EINVAL, "LM head needs %llu bytes of workspace; the static scratch holds %llu",
                 (unsigned long long)need, (unsigned long long)kScratchBytes);
