@@ -50,7 +50,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 #define GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define LPTR(p) ((__attribute__((address_space(3))) void*)(p))
 
-constexpr int BM = 256, BN = 256;
+constexpr int BM = 256, BN = 256, WAVES = 8;   // the 256-row kernel's tile and waves
 constexpr int GROUP_M = 4;
 
 __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
@@ -395,18 +395,11 @@ __device__ __forceinline__ void epilogue(const GemmParams& p, int64_t m, int n_l
   }
 }
 
-// Tile column of a wave's low 32-column block j; its partner is PAIR further.
-// 8 waves: wn = 0..3, one low block each; 4 waves: wn = 0..1, two each.
-template <int WAVES, int PAIR>
-__device__ __forceinline__ int lo_col(int wn, int j) {
-  if constexpr (WAVES == 8) {
-    constexpr int PW = PAIR / 32;
-    return (wn / PW) * (2 * PAIR) + (wn % PW) * 32;
-  } else {
-    if constexpr (PAIR == 32) return wn * 128 + j * 64;
-    else if constexpr (PAIR == 64) return wn * 128 + j * 32;
-    else return wn * 64 + j * 32;
-  }
+// Tile column of a wave's low 32-column block; its partner is PAIR further.
+template <int PAIR>
+__device__ __forceinline__ int lo_col(int wn) {
+  constexpr int PW = PAIR / 32;
+  return (wn / PW) * (2 * PAIR) + (wn % PW) * 32;
 }
 
 // -------------------------------------------------------------- the kernels
@@ -422,12 +415,11 @@ __device__ __forceinline__ void stage_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// Wait until at most N of the wave's copies are still in flight.
 template <int N>
-__device__ __forceinline__ void wait_vm() {
-  if constexpr (N == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  else if constexpr (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-  else if constexpr (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-  else asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+__device__ __forceinline__ void wait_copies() {
+  static_assert(N <= 63, "the wait counter holds 6 bits");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
 // First column of tile tn: a gate/up tile holds 128 FFN columns of each half.
@@ -588,7 +580,6 @@ __device__ __forceinline__ TileCoord tile_of(const GemmParams& p) {
 }
 
 // ---------------------------------------------------------- 256-row tiles, BK = 64
-template <int WAVES>
 struct Kc2Rows {
   const uint16_t* row[32 / WAVES];
   int c8;
@@ -596,9 +587,8 @@ struct Kc2Rows {
 
 // Copy q of wave w moves rows 8 kb + lane/8, kb = w + WAVES q; (row >> 1) & 7 =
 // 4 (w & 1) + lane/16 is the same for every q.
-template <int WAVES>
-__device__ __forceinline__ Kc2Rows<WAVES> kc2_rows(const Operand& op, int x0, int tile_idx, int wave, int lane) {
-  Kc2Rows<WAVES> r;
+__device__ __forceinline__ Kc2Rows kc2_rows(const Operand& op, int x0, int tile_idx, int wave, int lane) {
+  Kc2Rows r;
   r.c8 = 8 * ((lane & 7) ^ (4 * (wave & 1) + (lane >> 4)));
 #pragma unroll
   for (int q = 0; q < 32 / WAVES; ++q) {
@@ -618,8 +608,8 @@ __device__ __forceinline__ Kc2Rows<WAVES> kc2_rows(const Operand& op, int x0, in
 }
 
 // RAGGED: K may end inside the stage (or before it); chunks past it copy zeros.
-template <int WAVES, bool RAGGED>
-__device__ __forceinline__ void copy2_kc(uint8_t* lds, const Kc2Rows<WAVES>& rows, int k0, int K, int wave) {
+template <bool RAGGED>
+__device__ __forceinline__ void copy2_kc(uint8_t* lds, const Kc2Rows& rows, int k0, int K, int wave) {
   const int k = k0 + rows.c8;
 #pragma unroll
   for (int q = 0; q < 32 / WAVES; ++q)
@@ -680,7 +670,6 @@ struct Mn2Rows {
   uint32_t off0;   // element offset of the lane's 16 bytes for copy 0 at k0 = 0
 };
 
-template <int WAVES>
 __device__ __forceinline__ Mn2Rows mn2_rows(const Operand& op, int x0, int wave, int lane) {
   const int kr = 2 * wave + (lane >> 5);
   const int lc = (lane & 31) ^ mn_swz<256>(kr);
@@ -689,7 +678,7 @@ __device__ __forceinline__ Mn2Rows mn2_rows(const Operand& op, int x0, int wave,
   return Mn2Rows{static_cast<uint32_t>(kr * op.src.ld + x)};
 }
 
-template <int WAVES, bool RAGGED, int MAP>
+template <bool RAGGED, int MAP>
 __device__ __forceinline__ void copy2_mn(uint8_t* lds, const Operand& op, const Mn2Rows& rows, int x0, int k0, int K,
                                          int wave, int lane) {
   // A stage's 64 k-rows are consecutive in memory when the operand is one
@@ -769,29 +758,27 @@ __device__ __forceinline__ void interleave2() {
 // The BK = 64 main loop of one tile over its stages [kb, kb + n), n even:
 // products added into acc.  The four stage buffers a0 b0 a1 b1 (32 KB each)
 // hold two stages.
-template <Layout LA, Layout LB, int WAVES, bool RAGGED, int MAP>
-__device__ __forceinline__ void mainloop64(const GemmParams& p, f32x16 (&acc)[4][WAVES == 8 ? 2 : 4], int tm, int tn,
+template <Layout LA, Layout LB, int NS, bool RAGGED, int MAP>
+__device__ __forceinline__ void mainloop64(const GemmParams& p, f32x16 (&acc)[4][NS], int tm, int tn,
                                            int kb, int n, uint8_t* a0, uint8_t* b0, uint8_t* a1, uint8_t* b1,
                                            int wave, int lane, int wm, const int* ncol) {
-  constexpr int NS = WAVES == 8 ? 2 : 4;
-  constexpr int PER = 32 / WAVES;           // copy instructions per operand per stage per wave
   const int m0 = tm * BM, n0 = tn * BN;
-  Kc2Rows<WAVES> ra{}, rb{};
+  Kc2Rows ra{}, rb{};
   Mn2Rows ma{}, mb{};
-  if constexpr (LA == Layout::KC) ra = kc2_rows<WAVES>(p.A, m0, tm, wave, lane);
-  else ma = mn2_rows<WAVES>(p.A, m0, wave, lane);
-  if constexpr (LB == Layout::KC) rb = kc2_rows<WAVES>(p.B, n0, tn, wave, lane);
-  else mb = mn2_rows<WAVES>(p.B, n0, wave, lane);
+  if constexpr (LA == Layout::KC) ra = kc2_rows(p.A, m0, tm, wave, lane);
+  else ma = mn2_rows(p.A, m0, wave, lane);
+  if constexpr (LB == Layout::KC) rb = kc2_rows(p.B, n0, tn, wave, lane);
+  else mb = mn2_rows(p.B, n0, wave, lane);
   // stage kt of the range (stages past its end repeat the last one: the wait counts stay fixed)
   auto issue_a = [&](int kt, uint8_t* la) {
     const int k0 = (kb + min(kt, n - 1)) * BK2;
-    if constexpr (LA == Layout::KC) copy2_kc<WAVES, RAGGED>(la, ra, k0, p.K, wave);
-    else copy2_mn<WAVES, RAGGED, MAP>(la, p.A, ma, m0, k0, p.K, wave, lane);
+    if constexpr (LA == Layout::KC) copy2_kc<RAGGED>(la, ra, k0, p.K, wave);
+    else copy2_mn<RAGGED, MAP>(la, p.A, ma, m0, k0, p.K, wave, lane);
   };
   auto issue_b = [&](int kt, uint8_t* lb) {
     const int k0 = (kb + min(kt, n - 1)) * BK2;
-    if constexpr (LB == Layout::KC) copy2_kc<WAVES, RAGGED>(lb, rb, k0, p.K, wave);
-    else copy2_mn<WAVES, RAGGED, MAP>(lb, p.B, mb, n0, k0, p.K, wave, lane);
+    if constexpr (LB == Layout::KC) copy2_kc<RAGGED>(lb, rb, k0, p.K, wave);
+    else copy2_mn<RAGGED, MAP>(lb, p.B, mb, n0, k0, p.K, wave, lane);
   };
 
   Frags2<NS> f0, f1;
@@ -816,7 +803,7 @@ __device__ __forceinline__ void mainloop64(const GemmParams& p, f32x16 (&acc)[4]
     read_frags2<LA, LB, NS>(f1, xa, xb, wm, ncol, 3, lane);
     mfma_frags2<NS>(acc, f0);
     interleave2<LA, LB, NS>();
-    wait_vm<0>();
+    wait_copies<0>();
     stage_barrier();
     issue_a(kt + 2, xa);
     // Keep the copies here, right after the barrier: left alone, the scheduler
@@ -832,29 +819,27 @@ __device__ __forceinline__ void mainloop64(const GemmParams& p, f32x16 (&acc)[4]
   issue_b(0, b0);
   issue_a(1, a1);
   issue_b(1, b1);
-  if constexpr (PER == 8) wait_vm<16>();
-  else wait_vm<8>();
+  wait_copies<8>();      // stage 0 is there; the 4 + 4 copies of stage 1 may be in flight
   stage_barrier();
   read_frags2<LA, LB, NS>(f0, a0, b0, wm, ncol, 0, lane);
   for (int kt = 0; kt < n; kt += 2) {
     stage(kt, a0, b0, a1, b1);
     stage(kt + 1, a1, b1, a0, b0);
   }
-  wait_vm<0>();      // the last (repeated) stage copy has landed
+  wait_copies<0>();      // the last (repeated) stage copy has landed
 }
 
 // Wave-private staging space of the epilogue in the stage buffers.
-template <int WAVES>
 __device__ __forceinline__ float* stage_space(uint8_t* a0, uint8_t* b0, uint8_t* a1, uint8_t* b1, int wave) {
-  const int q = WAVES == 8 ? (wave >> 1) : wave;
+  const int q = wave >> 1;
   uint8_t* mine = q == 0 ? a0 : q == 1 ? b0 : q == 2 ? a1 : b1;
-  if constexpr (WAVES == 8) mine += (wave & 1) * 16384;
+  mine += (wave & 1) * 16384;
   return reinterpret_cast<float*>(mine);
 }
 
-template <Layout LA, Layout LB, EpiKind KIND, int PAIR, int WAVES, bool RAGGED, int MAP>
+template <Layout LA, Layout LB, EpiKind KIND, int PAIR, bool RAGGED, int MAP>
 __global__ void __launch_bounds__(WAVES * 64, 1) gemm_bk64(GemmParams p) {
-  constexpr int NS = WAVES == 8 ? 2 : 4;
+  constexpr int NS = 2;      // 32-column blocks of a wave
   __shared__ __attribute__((aligned(16))) uint8_t a0[TILE2], b0[TILE2], a1[TILE2], b1[TILE2];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform per wave: scalar code for wave-level decisions
@@ -867,12 +852,11 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemm_bk64(GemmParams p) {
   const int part = pid_all / tiles;
   const TileCoord tc = tile_coord(p, pid_all - part * tiles);
   const int tm = tc.tm, tn = tc.tn, m0 = tm * BM;
-  const int wm = WAVES == 8 ? (wave >> 2) : (wave >> 1);
-  const int wn = WAVES == 8 ? (wave & 3) : (wave & 1);
+  const int wm = wave >> 2, wn = wave & 3;
   int ncol[NS];
 #pragma unroll
   for (int j = 0; j < NS / 2; ++j) {
-    ncol[j] = lo_col<WAVES, PAIR>(wn, j);
+    ncol[j] = lo_col<PAIR>(wn);
     ncol[j + NS / 2] = ncol[j] + PAIR;
   }
   // stages per part, even; past the end of K they hold zeros (only without a split)
@@ -894,7 +878,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemm_bk64(GemmParams p) {
 #pragma unroll
     for (int j = 0; j < NS; ++j) acc[i][j] = f32x16{};
   // Unless RAGGED, K is a multiple of 2 * BK2 * parts.
-  mainloop64<LA, LB, WAVES, RAGGED, MAP>(p, acc, tm, tn, part * n_st, n_st, a0, b0, a1, b1, wave, lane, wm, ncol);
+  mainloop64<LA, LB, NS, RAGGED, MAP>(p, acc, tm, tn, part * n_st, n_st, a0, b0, a1, b1, wave, lane, wm, ncol);
   // The fp32 accumulate: the products start from zero and part 0 adds the C
   // tile in the epilogue, whose loads overlap its stores (loading C into the
   // accumulators before the first product measured 2-3% slower on the largest
@@ -907,7 +891,7 @@ __global__ void __launch_bounds__(WAVES * 64, 1) gemm_bk64(GemmParams p) {
     acc_store_f32<NS>(acc, p, cbase, ldc, static_cast<int64_t>(m0) + wm * 128, tn, ncol, lane);
   } else {
     __syncthreads();   // every wave is done reading the stages
-    store_tile<KIND, PAIR, NS>(p, acc, stage_space<WAVES>(a0, b0, a1, b1, wave), static_cast<int64_t>(m0) + wm * 128,
+    store_tile<KIND, PAIR, NS>(p, acc, stage_space(a0, b0, a1, b1, wave), static_cast<int64_t>(m0) + wm * 128,
                                tn, ncol, lane);
   }
 }
@@ -1030,12 +1014,6 @@ __device__ __forceinline__ StageSrc<T / (8 * W)> tile_src_mn(const Operand& op, 
     r.g[q] = k0 + kr < K ? sr.row(op.src, kr) + x : zeros();
   }
   return r;
-}
-
-template <int N>
-__device__ __forceinline__ void wait_copies() {
-  static_assert(N <= 63, "the wait counter holds 6 bits");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
 template <Layout LA, Layout LB, EpiKind KIND, int T, int W, int S, int MAP, bool STREAM>
@@ -1280,9 +1258,9 @@ hipError_t launch256(const GemmParams& p, hipStream_t stream) {
   if (KIND == EpiKind::AccF32 && p.epi.ldc > (int64_t{1} << 21)) return hipErrorInvalidValue;
   const dim3 grid(tiles_m * tiles_n * parts);
   if (p.K % (2 * BK2) == 0)
-    hipLaunchKernelGGL((gemm_bk64<LA, LB, KIND, PAIR, 8, false, MAP>), grid, dim3(512), 0, stream, p);
+    hipLaunchKernelGGL((gemm_bk64<LA, LB, KIND, PAIR, false, MAP>), grid, dim3(512), 0, stream, p);
   else
-    hipLaunchKernelGGL((gemm_bk64<LA, LB, KIND, PAIR, 8, true, MAP>), grid, dim3(512), 0, stream, p);
+    hipLaunchKernelGGL((gemm_bk64<LA, LB, KIND, PAIR, true, MAP>), grid, dim3(512), 0, stream, p);
   return hipGetLastError();
 }
 template <Layout LA, Layout LB, EpiKind KIND, int PAIR>
@@ -1328,8 +1306,6 @@ hipError_t gemm(const GemmParams& params, Layout la, Layout lb, hipStream_t stre
     if (k == E::SwiGLUBwd) return launch<L::KC, L::MN, E::SwiGLUBwd, 128>(p, stream);
     if (k == E::ResidualSP) return launch<L::KC, L::MN, E::ResidualSP, 128>(p, stream);
     if (k == E::StoreBF16) return launch<L::KC, L::MN, E::StoreBF16, 128>(p, stream);
-    if (k == E::StoreF32) return launch<L::KC, L::MN, E::StoreF32, 128>(p, stream);
-    if (k == E::AccF32) return launch<L::KC, L::MN, E::AccF32, 128>(p, stream);
   } else if (la == L::MN && lb == L::MN) {
     if (k == E::AccF32) return launch<L::MN, L::MN, E::AccF32, 128>(p, stream);
   }
