@@ -10,8 +10,8 @@
 // gfx950 design:
 //  * every K/V/Q/dO tile is copied global -> LDS with global_load_lds_dwordx4
 //    (no staging registers) into a row-major tile with an XOR swizzle of its
-//    16-byte chunks; two separate LDS buffers alternate so that the next tile
-//    streams in while the current one is used;
+//    16-byte chunks; two buffers alternate (forward, dQ), or a ring of four turns
+//    (dK/dV), so that the next tiles stream in while the current one is used;
 //  * operands that need the token index contiguous (V in P V, Q and dO in the
 //    dK/dV products, K in dQ) are read transposed straight from those tiles
 //    with ds_read_b64_tr_b16 (16 lanes x 4 rows -> 4 rows per lane);
@@ -20,7 +20,8 @@
 //    probabilities then feed the next MFMA from registers with the
 //    contraction index permuted consistently on both operands;
 //  * masks are applied only on tiles that straddle the diagonal;
-//  * 256 threads and 64 KB of LDS per workgroup: two workgroups per CU.
+//  * forward and dQ: 256 threads and at most 64 KB of LDS, two workgroups per
+//    CU; dK/dV: 512 threads and 97 KB, one workgroup per CU, two waves per SIMD.
 //  * dK/dV are accumulated over the query heads of a kv-head inside one
 //    workgroup, or, when that leaves too few workgroups, over a slice of them
 //    with an fp32 partial per slice that a small kernel sums: no atomics, the
@@ -49,7 +50,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr int KT = 64;            // keys per tile (forward, dQ)
+constexpr int KT = 64;            // keys per tile (forward; dQ takes 32)
 constexpr int QT = 32;            // queries per tile (dK/dV)
 constexpr int kDkvStages = 4;     // dK/dV: query tiles in the copy ring (even: the handover buffer is the stage's parity)
 // LDS fragment reads kept in flight ahead of the products, per kernel
@@ -1043,7 +1044,7 @@ hipError_t fwd_impl(const AttnParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Host copy of the query-tile walk of the dK/dV kernel: the number of 64-query
+// Host copy of the query-tile walk of the dK/dV kernel: the number of QT-query
 // tiles a 128-key block starting at global position kpos0 visits per head.
 int dkdv_tiles(const AttnParams& p, int kpos0) {
   const int n_qt = (p.n_q + QT - 1) / QT;
@@ -1096,7 +1097,11 @@ hipError_t bwd_impl(const AttnParams& p, int part, hipStream_t stream) {
 
 int attn_bwd_splits(const AttnParams& p) {
   // Split the query heads of a kv-head over workgroups until the dK/dV grid
-  // has at least 512 workgroups (two per CU) or every head has its own.
+  // has at least 512 workgroups or every head has its own.  One workgroup runs on
+  // a CU at a time, and under the causal mask they differ in length: two per CU
+  // let the short ones fill up behind the long ones.  Stopping at 256: 312 + 14 us (the
+  // sum of the partials) -> 471 + 10 on the 70B TP8 shard, 301 + 20 -> 458 on 8B
+  // TP2 CP2; grids that reach neither number are not touched.
   const int group = p.a_t / p.k_t;
   const int base = count_blocks(p, 128) * p.k_t * p.b;
   int n = 1;

@@ -98,9 +98,10 @@ struct GemmParams {
   EpiParams epi;
   int32_t tile;                // rows of the kernel's square tile: 256, 128 or 64 (0 = 256)
   int32_t pair;                // distance of the epilogue's column pairs (QkvRope: d_h/2, SwiGLUFwd: f), set by gemm()
-  // AccF32 and StoreBF16 only: the K range is cut into k_splits equal parts
-  // (0 or 1 = none).  AccF32: part 0 accumulates into C; part s > 0 stores its
-  // fp32 sum to partial + (s - 1) M N (row-major, ld N), which
+  // AccF32 and StoreBF16 only: the K range is cut into k_splits parts (0 or 1 =
+  // none), equal ones on 256-row tiles, elsewhere of whole 64-k stages, of which the
+  // last part may have fewer, or none.  AccF32: part 0 accumulates into C; part
+  // s > 0 stores its fp32 sum to partial + (s - 1) M N (row-major, ld N), which
   // gemm_split_reduce then adds to C in order s = 1, 2, ...  StoreBF16: part s
   // stores to partial + s M N and gemm_split_store writes bf16(sum) to C.
   int32_t k_splits;

@@ -42,9 +42,10 @@ constexpr int kMaxChunks = 16;   // h <= 64 lanes * 16 chunks * 8 = 8192
 
 // Entry idx of the cos/sin table.  The table has no launch of its own: its
 // entries are extra blocks of a kernel that runs ahead of the first reader anyway
-// (the first norm in the forward, the second norm's gain sum in the backward),
-// where double-precision work on a few CUs hides beside the rows; alone it cost
-// 3 (16 blocks) to 5 us (2048 blocks) a pass.
+// (the first norm in the forward, the second norm's gain sum in the backward).
+// That saves the launch (6 to 7 us timed alone) but not all of the
+// double-precision work: the first norm takes 0.8 us longer on 2000 tokens (8B TP4),
+// 2.7 on 4096 of head size 128 (7B), 4.8 to 6.8 on the 8B and 70B shards.
 __device__ __forceinline__ void rope_entry(const RopeTable& r, int64_t idx) {
   const int half = r.d_h / 2;
   if (idx >= static_cast<int64_t>(r.rows) * half) return;
@@ -331,7 +332,8 @@ __global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(
 // atomics): a block of 16 waves per 64 columns, wave w taking rows w, w + 16, ..,
 // all their loads in flight at once, since the kernel's time is the latency of
 // its loads (128 rows of 256 columns 4.0 -> 2.0 us, 256 rows of 2048 to 8192
-// columns 7 -> 4.7 us against 4 waves with 4 loads in flight each).  ROPE: the blocks past the columns fill the RoPE table.
+// columns 7 -> 4.7 us against 4 waves with 4 loads in flight each).  ROPE: the
+// blocks past the columns fill the RoPE table.
 constexpr int kSumWaves = 16, kSumRows = 256 / kSumWaves;
 template <bool ROPE>
 __global__ void __launch_bounds__(kSumWaves * 64) column_sums_kernel(const float* __restrict__ partial, int32_t n,
@@ -611,8 +613,9 @@ __global__ void __launch_bounds__(256) embed_fwd_kernel(const int64_t* __restric
 // workspace: the stashed ids stay, so a captured backward can be replayed), a
 // workgroup walks a window of kEmbWin sorted tokens over 1024 columns and adds
 // each run of equal ids up in registers before one atomic add per column,
-// consecutive lanes on consecutive columns.  8192 tokens of hidden 4096 over a shard of 32064 (heavy-tailed ids,
-// a quarter of them in the shard): 627 -> 15 (sort) + 28 us.
+// consecutive lanes on consecutive columns.  8192 tokens of hidden 4096 over a
+// shard of 32064 (heavy-tailed ids, a quarter of them in the shard): 627 -> 15
+// (sort) + 28 us.
 constexpr int kEmbChunk = 2048, kEmbWin = 16;
 
 // Keys (id - v0) << 32 | token, out-of-range ids as all ones, sorted ascending
