@@ -520,7 +520,7 @@ uint64_t partial_bytes(int64_t M, int64_t N, int splits, bool acc_f32) {
 
 uint64_t split_ws_bytes(int64_t M, int64_t N, int64_t K, bool acc_f32 = true) {
   const EpiKind kind = acc_f32 ? EpiKind::AccF32 : EpiKind::StoreBF16;
-  return partial_bytes(M, N, gemm_plan(M, N, K, kind, gemm_max_splits(M, N, K, acc_f32)).splits, acc_f32);
+  return partial_bytes(M, N, gemm_plan(M, N, K, kind, gemm_max_splits(M, N, K, acc_f32), true).splits, acc_f32);
 }
 
 FwdWs plan_fwd(const Shard& x, const l4d_peer_outputs* sends) {
@@ -670,7 +670,8 @@ inline EpiParams epi_store(void* c, int64_t ldc) {
 }
 
 // split_ws: room for the fp32 partials of a K range cut into at most max_splits
-// parts (AccF32 and StoreBF16 only; 0 = the layer's rule; NULL = never split).
+// parts (AccF32 and StoreBF16 only; 0 = a product of the layer backward, by its
+// rules; NULL = never split).
 int run_gemm(const char* name, hipStream_t s, int64_t M, int64_t N, int64_t K, Operand A, Layout la, Operand B,
              Layout lb, EpiParams e, float* split_ws = nullptr, int max_splits = 0) {
   GemmParams p{};
@@ -681,10 +682,12 @@ int run_gemm(const char* name, hipStream_t s, int64_t M, int64_t N, int64_t K, O
   p.B = B;
   p.epi = e;
   const bool acc = e.kind == EpiKind::AccF32;
+  const bool layer = split_ws && max_splits == 0;
   if (!split_ws || !(acc || e.kind == EpiKind::StoreBF16)) max_splits = 1;
-  else if (max_splits == 0) max_splits = gemm_max_splits(M, N, K, acc);
-  const GemmPlan plan = gemm_plan(M, N, K, e.kind, max_splits);
+  else if (layer) max_splits = gemm_max_splits(M, N, K, acc);
+  const GemmPlan plan = gemm_plan(M, N, K, e.kind, max_splits, layer);
   p.tile = plan.tile;
+  p.stream_c = plan.stream_c;
   p.k_splits = plan.splits;
   p.partial = split_ws;
   int rc = launch(name, s, [&] { return gemm(p, la, lb, s); });

@@ -1219,18 +1219,11 @@ __global__ void __launch_bounds__(W * 64) gemm_tile(GemmParams p) {
   }
 }
 
-// A weight gradient of this size is streamed past the caches, as the 256-row
-// kernel does with all of them: left there it displaces the operands of the
-// kernels that follow (a layer of hidden 2048, FFN 5464 on 1000 tokens 677 us, streamed
-// 630; hidden 4096, FFN 11008 on TP 4, 1024 tokens 637 and 602), while smaller ones
-// are found there by the next call (hidden 1024 on 1000 tokens 302, streamed 307).
-constexpr int64_t kStreamBytes = 32 << 20;
-
 template <Layout LA, Layout LB, EpiKind KIND, int T, int W, int S, int MAP>
 hipError_t launch_tile(const GemmParams& p, hipStream_t stream) {
   const int parts = p.k_splits > 1 ? p.k_splits : 1;
   const dim3 grid(static_cast<unsigned>((p.M + T - 1) / T) * ((p.N + T - 1) / T) * parts);
-  if (KIND == EpiKind::AccF32 && static_cast<int64_t>(p.M) * p.N * 4 >= kStreamBytes)
+  if (KIND == EpiKind::AccF32 && p.stream_c)
     hipLaunchKernelGGL((gemm_tile<LA, LB, KIND, T, W, S, MAP, KIND == EpiKind::AccF32>), grid, dim3(W * 64), 0, stream, p);
   else
     hipLaunchKernelGGL((gemm_tile<LA, LB, KIND, T, W, S, MAP, false>), grid, dim3(W * 64), 0, stream, p);
@@ -1413,8 +1406,8 @@ constexpr GridCost kForward[5] = {{256, 256, 8.0, 4.8, 1.0, 0.65},
                                   {128, 512, 5.0, 4.8, 0.25, 0.85},
                                   {64, 256, 4.0, 4.8, 0.15, 0.06},
                                   {64, 512, 4.0, 4.8, 0.20, 0.32}};
-// Weight gradients (both operands transposed, C read and written): fits to 393
-// of them, hidden 256 to 8192 and K 512 to 16384, each timed in 9 forms (rms error
+// Weight gradients of a layer (both operands transposed, C read and written):
+// fits to 393 of them, hidden 256 to 8192 and K 512 to 16384, each timed in 9 forms (rms error
 // 7 to 16% over the forms within 1.6 times the best).  The form picked takes 0.5% more
 // than the best one on average (at worst 27%: M 2752 N 4096 K 512, 46 us against
 // 36); with the constants above it took 2.7%, at worst 57% (M 4096 N 2752 K 1024: 82
@@ -1426,14 +1419,25 @@ constexpr GridCost kWeightGrad[5] = {{256, 256, 12.6, 8.9, 1.20, 0.40, 7.0, 23.0
                                      {128, 512, 11.6, 28.0, 0.73, 0.35},
                                      {64, 256, 8.3, 1e3, 0.24, 0.06},
                                      {64, 512, 5.9, 1e3, 0.34, 0.14}};
+// A layer's weight gradient of this size is streamed past the caches on small
+// tiles too, as the 256-row kernel does with all of them: left there it displaces
+// the operands of the kernels that follow (a layer of hidden 2048, FFN 5464 on
+// 1000 tokens 677 us, streamed 630; hidden 4096, FFN 11008 on TP 4, 1024 tokens 637
+// and 602), while smaller ones are found there by the next call (hidden 1024 on
+// 1000 tokens 302, streamed 307).  The head's weight gradient is the last product
+// of its call: whether streaming it pays depends on what the caller does next, and
+// timed in a row 64 tokens of a 16032-wide shard take 121 us streamed and 86 not,
+// of a 32064-wide one 268 and 327 (hidden 2048).  It stays as it was: 256-row tiles
+// (streamed) or, where kForward prefers them, smaller ones (not).
+constexpr int64_t kStreamBytes = 32 << 20;
 }  // namespace
 
-GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, EpiKind kind, int max_splits) {
-  const bool acc = kind == EpiKind::AccF32;
-  const GridCost* cost = acc ? kWeightGrad : kForward;
+GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, EpiKind kind, int max_splits, bool layer) {
+  const bool acc = kind == EpiKind::AccF32, layer_dw = layer && acc;
+  const GridCost* cost = layer_dw ? kWeightGrad : kForward;
   const int64_t stages = (K + BK2 - 1) / BK2;
   const double mn = static_cast<double>(M) * N;
-  GemmPlan best{256, 1};
+  GemmPlan best{256, 1, layer_dw && static_cast<int64_t>(4 * mn) >= kStreamBytes};
   double best_us = 1e30;
   for (int s = 1; s <= max_splits; ++s) {
     if (s > 1 && (N % 4 != 0 || stages < 4 * s)) break;
@@ -1447,18 +1451,20 @@ GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, EpiKind kind, int max_splits
       // Parts store 4 bytes an element, but for part 0 of an accumulate, which reads
       // and writes C.  The reduce pass reads the partials and writes C (an
       // accumulate reads it too), 5.7 us and 6.9 TB/s over 5 to 55 us.  The price of
-      // dX parts on small tiles stands for their stores as well.
+      // other parts (dX on small tiles, the head's d_hidden, whose workspace would
+      // grow with more of them) stands for their stores as well.
       double c_bytes = 8.0, reduce = 0.0;
-      if (s > 1) {
+      if (s > 1 && (layer_dw || (layer && g.T == 256))) {
         reduce = 5.7 + (4.0 * n_part + (acc ? 8.0 : 2.0)) * mn / 6.9e6;
-        if (acc) c_bytes = (8.0 + 4.0 * n_part) / s;
-        else if (g.T == 256) c_bytes = 4.0;
-        else reduce = 4.0 + n_part * 8.0 * mn / 4e6;
+        c_bytes = acc ? (8.0 + 4.0 * n_part) / s : 4.0;
+      } else if (s > 1) {
+        reduce = 4.0 + n_part * 8.0 * mn / 4e6;
       }
       const double us = reduce + grid_us(g, tiles, g.T == 256 ? (st + 1) / 2 * 2 : st, c_bytes) +
                         (M % g.T ? g.m_edge : 0.0) + (N % g.T ? g.n_edge : 0.0);
       if (us < 0.97 * best_us) {       // a split or a smaller tile has to win by a margin
-        best = GemmPlan{g.T, s};
+        best.tile = g.T;
+        best.splits = s;
         best_us = us;
       }
     }

@@ -97,6 +97,7 @@ struct GemmParams {
   Operand A, B;
   EpiParams epi;
   int32_t tile;                // rows of the kernel's square tile: 256, 128 or 64 (0 = 256)
+  bool stream_c;               // small tiles: C is read and written past the caches (AccF32)
   int32_t pair;                // distance of the epilogue's column pairs (QkvRope: d_h/2, SwiGLUFwd: f), set by gemm()
   // AccF32 and StoreBF16 only: the K range is cut into k_splits parts (0 or 1 =
   // none), equal ones on 256-row tiles, elsewhere of whole 64-k stages, of which the
@@ -111,11 +112,14 @@ struct GemmParams {
 hipError_t gemm(const GemmParams& p, Layout la, Layout lb, hipStream_t stream);
 // The tile size of a GEMM and the parts its K range is cut into: at most
 // max_splits (1 = none; only AccF32 and StoreBF16 can split, into a workspace of
-// splits - 1, for StoreBF16 splits, fp32 M x N partials).
+// splits - 1, for StoreBF16 splits, fp32 M x N partials).  layer: a product of the
+// layer backward, not of the head; its splits and weight gradients are priced, and
+// the gradients streamed, by rules of their own.
 struct GemmPlan {
   int32_t tile, splits;
+  bool stream_c;
 };
-GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, EpiKind kind, int max_splits);
+GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, EpiKind kind, int max_splits, bool layer = false);
 // The largest split the layer's workspace is planned for (1 = none).
 int gemm_max_splits(int64_t M, int64_t N, int64_t K, bool acc_f32);
 // C[m][n] += sum over s of partial[s][m][n], s = 0 .. splits - 2, in that order.

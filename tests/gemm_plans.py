@@ -9,13 +9,14 @@ STORE_BF16, ACC_F32 = 0, 2        # EpiKind
 
 
 class _Plan(C.Structure):
-    _fields_ = [("tile", C.c_int32), ("splits", C.c_int32)]
+    _fields_ = [("tile", C.c_int32), ("splits", C.c_int32), ("stream_c", C.c_bool)]
 
 
 def plan(M, N, K, kind, max_splits):
-    f = L.lib()._ZN3l4d9gemm_planElllNS_7EpiKindEi
-    f.argtypes, f.restype = [C.c_int64] * 3 + [C.c_int, C.c_int], _Plan
-    p = f(M, N, K, kind, max_splits)
+    """Of a product of the layer backward."""
+    f = L.lib()._ZN3l4d9gemm_planElllNS_7EpiKindEib
+    f.argtypes, f.restype = [C.c_int64] * 3 + [C.c_int, C.c_int, C.c_bool], _Plan
+    p = f(M, N, K, kind, max_splits, True)
     return p.tile, p.splits
 
 
